@@ -1441,26 +1441,42 @@ hipError_t launch_head(const HeadArgs& a, hipStream_t stream) {
 
 namespace {
 
-// Category-prior head: l[b, z] = sum_j U[z, j] h_anchor[b, j] + e[z] in fp32 accumulation.
-// One workgroup per block; every category's dot product is a workgroup reduction.
+// Category-prior head: l[b, z] = sum_j U[z, j] h_anchor[b, j] + e[z] in fp32 accumulation, one
+// 256-thread workgroup per (block, category). Bound by latency (8 KB per operand row at d = 4096,
+// U re-read from L2 by every block): with 16-byte loads a thread has its two loads per 2048
+// hidden units in flight at once, and one reduction per workgroup follows. One workgroup per
+// block walking its categories, with 2-byte loads and a reduction each, took 39 us for 16 blocks
+// of 8 categories at d = 4096 (20 us for one block of 4 at d = 2560); this form takes 4.7 us
+// (5.1 us).
+// VEC: d % 8 == 0, so every row is 16-byte aligned.
+template <bool VEC>
 __global__ __launch_bounds__(256) void prior_head_kernel(const __bf16* __restrict__ ha,
                                                          const __bf16* __restrict__ U,
                                                          const __bf16* __restrict__ e,
                                                          float* __restrict__ ell, int R, int d) {
   __shared__ float red[4];
   const int64_t b = blockIdx.x;
+  const int z = blockIdx.y;
   const __bf16* hb = ha + b * d;
-  for (int z = 0; z < R; ++z) {
-    const __bf16* u = U + static_cast<int64_t>(z) * d;
-    float s = 0.0f;
+  const __bf16* u = U + static_cast<int64_t>(z) * d;
+  float s = 0.0f;
+  if constexpr (VEC) {
+#pragma unroll 2
+    for (int j = 8 * static_cast<int>(threadIdx.x); j < d; j += 2048) {
+      const bf16x8 x = *reinterpret_cast<const bf16x8*>(hb + j);
+      const bf16x8 y = *reinterpret_cast<const bf16x8*>(u + j);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) s = fmaf(static_cast<float>(y[i]), static_cast<float>(x[i]), s);
+    }
+  } else {
     for (int j = threadIdx.x; j < d; j += 256)
       s = fmaf(static_cast<float>(u[j]), static_cast<float>(hb[j]), s);
-    s = wave_sum(s);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) ell[b * R + z] = ((red[0] + red[1]) + (red[2] + red[3])) + static_cast<float>(e[z]);
-    __syncthreads();
   }
+  s = wave_sum(s);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    ell[b * R + z] = ((red[0] + red[1]) + (red[2] + red[3])) + static_cast<float>(e[z]);
 }
 
 }  // namespace
@@ -1516,9 +1532,16 @@ hipError_t launch_expand(const ExpandArgs& a, hipStream_t stream) {
 
 hipError_t launch_prior_head(const PriorHeadArgs& a, hipStream_t stream) {
   if (a.B > 0x7fffffff) return hipErrorInvalidConfiguration;
-  hipLaunchKernelGGL(prior_head_kernel, dim3(static_cast<unsigned>(a.B)), dim3(256), 0, stream,
-                     static_cast<const __bf16*>(a.h_anchor), static_cast<const __bf16*>(a.U),
-                     static_cast<const __bf16*>(a.e), a.ell, a.R, a.d);
+  const dim3 grid(static_cast<unsigned>(a.B), static_cast<unsigned>(a.R));
+  const __bf16* ha = static_cast<const __bf16*>(a.h_anchor);
+  const __bf16* U = static_cast<const __bf16*>(a.U);
+  const __bf16* e = static_cast<const __bf16*>(a.e);
+  if (a.d % 8 == 0)
+    hipLaunchKernelGGL(prior_head_kernel<true>, grid, dim3(256), 0, stream, ha, U, e, a.ell, a.R,
+                       a.d);
+  else
+    hipLaunchKernelGGL(prior_head_kernel<false>, grid, dim3(256), 0, stream, ha, U, e, a.ell,
+                       a.R, a.d);
   return hipGetLastError();
 }
 

@@ -130,3 +130,14 @@ def test_prior_head_parity(case):
     want = EX.prior_logits(_np(ha), _np(U), _np(e))
     bound = 1e-5 * (np.abs(_np(ha)) @ np.abs(_np(U)).T + np.abs(_np(e))) + 1e-6
     assert np.all(np.abs(ell.cpu().numpy() - want) <= bound)
+
+
+# Hidden sizes at the edges of the 16-byte load path: one load of one thread, no multiple of 8 (the
+# scalar path), just below and above one round of the workgroup's 2048 units, a ragged third round.
+PRIOR_EDGES = [("one-load", 2, 1, 8), ("scalar", 2, 3, 77), ("below-a-round", 1, 5, 2040),
+               ("past-a-round", 3, 2, 2056), ("third-round", 2, 64, 4104)]
+
+
+@pytest.mark.parametrize("case", PRIOR_EDGES, ids=[c[0] for c in PRIOR_EDGES])
+def test_prior_head_edges(case):
+    test_prior_head_parity(case)
