@@ -87,3 +87,21 @@ def test_objective_random_shapes():
         zt = float(rng.choice([0.0, 0.5, 1.0, 2.0]))
         tau = float(rng.choice([1e-4, 0.05, 0.1, 0.5, 0.9]))
         _objective_case(f"random-{i}", B, K, R, V, 8, target, T, zt, tau, 500 + i)
+
+
+# Edges of the parallel form: one position, a full and an overfull second round of 64 positions,
+# every lane-segment width, K R and K at and past its limits (past them the walk takes over).
+EDGES = [
+    ("one-position", 3, 1, 1, 300, 8, "aligned", 1.0, 1.0, 0.1),
+    ("segments-16", 4, 20, 13, 300, 8, "aligned", 1.0, 1.0, 0.1),
+    ("segments-32", 4, 64, 32, 200, 8, "aligned", 1.0, 1.0, 1e-30),
+    ("kr-past-limit", 2, 33, 63, 200, 8, "aligned", 1.0, 1.0, 1e-30),
+    ("second-round", 2, 65, 3, 300, 8, "aligned", 1.0, 1.0, 1e-30),
+    ("k-at-limit", 2, 256, 8, 150, 8, "aligned", 1.0, 1.0, 1e-30),
+    ("k-past-limit", 2, 257, 2, 150, 8, "aligned", 1.0, 1.0, 1e-30),
+]
+
+
+@pytest.mark.parametrize("case", EDGES, ids=[c[0] for c in EDGES])
+def test_objective_edges(case):
+    _objective_case(*case, zlib.crc32(case[0].encode()))
