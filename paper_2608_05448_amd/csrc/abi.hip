@@ -98,9 +98,9 @@ WsLayout layout(int op, const dbl_shape& s) {
       sizes[1] = B * K * nchunk * sizeof(float);
       n = 2;
       break;
-    case DBL_OP_TARGET:  // rows B*K: per-segment candidate lists and their counts
-      sizes[0] = B * K * dbl::kFilterSegs * dbl::kFilterSegCap * sizeof(uint64_t);
-      sizes[1] = B * K * dbl::kFilterSegs * sizeof(int32_t);
+    case DBL_OP_TARGET:  // rows B*K: segment results, lists or bins, and the cut
+      sizes[0] = B * K * dbl::kFilterRowBytes;
+      sizes[1] = B * K * sizeof(dbl::FilterCut);
       n = 2;
       break;
     default:
@@ -580,8 +580,8 @@ dbl_status dbl_target_logprobs(int64_t N, int64_t V, const float* logits, float 
   a.top_p = top_p;
   a.logp = logp;
   if (use_ws) {
-    a.seg_cand = reinterpret_cast<uint64_t*>(static_cast<char*>(ws) + L.off[0]);
-    a.seg_count = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + L.off[1]);
+    a.row_ws = static_cast<char*>(ws) + L.off[0];
+    a.cuts = reinterpret_cast<dbl::FilterCut*>(static_cast<char*>(ws) + L.off[1]);
   }
   return hip_status(dbl::launch_filter(a, static_cast<hipStream_t>(stream)), "filter launch");
 }

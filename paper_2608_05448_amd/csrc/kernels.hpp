@@ -113,11 +113,15 @@ struct PriorHeadArgs {
   float* ell;            // [B, R]
 };
 
-// Target sampling transform: rows of logits -> filtered log-probabilities.
-// Rows of the target transform split over kFilterSegs workgroups keep up to kFilterSegCap
-// candidates each in the workspace.
-constexpr int kFilterSegs = 4;
-constexpr int kFilterSegCap = 1024;
+// Target sampling transform: rows of logits -> filtered log-probabilities. Per row the optional
+// workspace holds kFilterRowBytes (segment results, candidate lists or mass bins, by the filters
+// asked for) and 16 bytes for the row's cut.
+constexpr int kFilterRowBytes = 32768;
+struct FilterCut {
+  uint32_t key_above, key_at;  // logit keys at or above key_above are kept, and those at or above
+  uint32_t last_id;            // key_at whose id is at most last_id
+  uint32_t done;               // the row is already written
+};
 
 struct FilterArgs {
   int64_t N, V;
@@ -126,8 +130,8 @@ struct FilterArgs {
   int64_t top_k;        // 0: off
   float top_p;          // 1: off
   float* logp;          // [N, V]
-  uint64_t* seg_cand = nullptr;   // workspace [N, kFilterSegs, kFilterSegCap] or null
-  int32_t* seg_count = nullptr;   // workspace [N, kFilterSegs]
+  char* row_ws = nullptr;         // workspace [N, kFilterRowBytes] or null
+  FilterCut* cuts = nullptr;      // workspace [N]
 };
 
 // Early-determinism estimate from sampled target blocks.

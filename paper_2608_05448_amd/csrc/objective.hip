@@ -86,8 +86,8 @@ __global__ __launch_bounds__(64) void objective_kernel(ObjectiveArgs a) {
 // log pi_z + lq_{0,z} + ... + lq_{k,z} in position order, a segment of lanes per position takes
 // the log-sum-exp over categories, and wavefront 0 forms A_j, S_l and J with one position per
 // lane, the products and sums over positions in order. The same operations in the same order as
-// objective_kernel, whose walk waits for every position's gathers and reductions in turn: 39 -> 10 us at 32 blocks with
-// K = R = 16 (expected length and objective together 811 -> 786 us).
+// objective_kernel, whose walk waits for every position's gathers and reductions in turn:
+// 39 -> 10 us at 32 blocks with K = R = 16 (expected length and objective together 811 -> 786 us).
 constexpr int kObjMaxKR = 2048;
 constexpr int kObjMaxK = 256;
 

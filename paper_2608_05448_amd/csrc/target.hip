@@ -1,9 +1,9 @@
 // Target-side sampling transform and early-determinism estimate.
 //
-// filter   one 1024-thread workgroup per row: the target's logits divided by the temperature,
+// filter   one workgroup per row, or several (split rows, with a workspace): the logits divided by the temperature,
 //          restricted by top-k and then top-p, renormalised; -inf outside the kept set. Both cuts
-//          are exact radix selections over order-preserving 32-bit keys of s = fl32(logit / T)
-//          (four 8-bit digit passes with LDS histograms): by count for top-k (every value equal
+//          are exact selections over order-preserving 32-bit keys of s = fl32(logit / T), in
+//          general by radix (four 8-bit digit passes with LDS histograms): by count for top-k (every value equal
 //          to the k-th largest is kept), by the determinism contract's integer masses
 //          floor(detexp32(fl32(s - max)) 2^40) for top-p, where tokens are taken by decreasing s
 //          and, among equal s, increasing id, while the mass before them is below
@@ -184,15 +184,28 @@ __device__ __forceinline__ uint32_t wave_kth_largest(uint32_t t0, uint32_t t1, u
 constexpr int kFastK = 1024;
 constexpr int kCandCap = 4096;
 
-// Sorts a candidate list - visiting keys (key of s, ~id) of every token whose s is at least a
-// lower bound of the row's k-th largest s - in visiting order (s descending, id ascending),
-// applies both cuts and writes the kept tokens' log-probabilities; the rest of the output row
-// already holds -inf. Needs n >= k and n <= kCandCap; all kFT threads call it.
-// Sorts cand[0, n) (n <= kCandCap) in descending order: a bitonic network over the list padded
-// with zeros to a power of two (every visiting key has a nonzero low word, ids being below
-// 2^32 - 1). All kFT threads call it; it ends with a barrier.
+// Sorts cand[0, n) (n <= kCandCap, all keys different and nonzero) in descending order; all kFT
+// threads call it, and it ends with a barrier. Up to kRankMax keys, each thread counts the keys
+// larger than its own (LDS reads that all lanes share) and stores its key at that place: two
+// barriers, about 14 cycles per key, where the network below takes 300 per stage (28 stages for
+// 128 keys, 45 for 512). Above, a bitonic network over the list padded with zeros to a power of two
+// (every visiting key has a nonzero low word, ids being below 2^32 - 1).
+constexpr int kRankMax = 512;
+
 __device__ void block_sort_desc(uint64_t* cand, int n) {
   const int tid = threadIdx.x;
+  if (n <= kRankMax) {
+    const uint64_t mine = tid < n ? cand[tid] : 0;
+    int rank = 0;
+    if (tid < n) {
+#pragma unroll 8
+      for (int j = 0; j < n; ++j) rank += cand[j] > mine ? 1 : 0;
+    }
+    __syncthreads();
+    if (tid < n) cand[rank] = mine;
+    __syncthreads();
+    return;
+  }
   int np = 64;
   while (np < n) np <<= 1;
   for (int i = n + tid; i < np; i += kFT) cand[i] = 0;
@@ -215,36 +228,10 @@ __device__ void block_sort_desc(uint64_t* cand, int n) {
 }
 
 // Wavefront 0 alone, when the tokens tied with or above the k-th largest s number at most 64
-// (the usual case for small k): those nk tokens are gathered one per lane, sorted in visiting
-// order with a register bitonic network, and both cuts and the normaliser are wavefront
-// reductions, with no workgroup barrier. tk is the k-th largest key of the list.
-__device__ void finish_small(const FilterArgs& a, float* out, uint64_t* cand, int n,
-                             uint32_t tk, int nk) {
+// (the usual case for small k): e is lane l's token, the l-th in visiting order (0 from lane nk on);
+// both cuts and the normaliser are wavefront reductions, with no workgroup barrier.
+__device__ void finish_small(const FilterArgs& a, float* out, uint64_t e, int nk) {
   const int lane = lane_id();
-  // compact the nk entries with key >= tk to the front of the list, in list order (an entry
-  // moves only towards the front, past entries this wavefront has already read)
-  int base = 0;
-  for (int i0 = 0; i0 < n; i0 += 64) {
-    const int i = i0 + lane;
-    const uint64_t c = i < n ? cand[i] : 0;
-    const bool in = i < n && static_cast<uint32_t>(c >> 32) >= tk;
-    const uint64_t msk = __ballot(in);
-    if (in) cand[base + __popcll(msk & ((1ull << lane) - 1))] = c;
-    base += __popcll(msk);
-    asm volatile("" ::: "memory");
-  }
-  uint64_t e = lane < nk ? cand[lane] : 0;
-  // bitonic sort, descending, of one entry per lane (empty lanes hold 0)
-#pragma unroll
-  for (int size = 2; size <= 64; size <<= 1) {
-#pragma unroll
-    for (int stride = size >> 1; stride > 0; stride >>= 1) {
-      const uint64_t o = __shfl_xor(e, stride);
-      const bool desc = (lane & size) == 0;
-      const bool lower = (lane & stride) == 0;
-      e = (lower == desc) ? (e > o ? e : o) : (e < o ? e : o);
-    }
-  }
   const float sv = key_value(static_cast<uint32_t>(e >> 32));
   const float m = __shfl(sv, 0);
   int nkeep = nk;
@@ -265,61 +252,12 @@ __device__ void finish_small(const FilterArgs& a, float* out, uint64_t* cand, in
   }
 }
 
-__device__ void finish_candidates(const FilterArgs& a, float* out, uint64_t* cand, int n,
-                                  uint64_t* red, double* redd, int* sh_n) {
+// Both cuts, the normaliser and the kept tokens of a list sorted in visiting order that holds every
+// token at or above the row's k-th largest s (n >= k). All kFT threads call it.
+__device__ void finish_sorted(const FilterArgs& a, float* out, const uint64_t* cand, int n,
+                              uint64_t* red, double* redd) {
   const int tid = threadIdx.x;
   const int k = static_cast<int>(a.top_k);
-  // Wavefront 0: the k-th largest key of the list (bisection with ballots over the list) and
-  // how many entries are at or above it.
-  if (tid < 64) {
-    uint64_t lo = 0, hi = 0xFFFFFFFFu;
-    int c = 0;
-    if (n <= 8 * 64) {  // up to 8 keys per lane, in registers; counts by ballot
-      uint32_t kk[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int i = tid + 64 * j;
-        kk[j] = i < n ? static_cast<uint32_t>(cand[i] >> 32) : 0;
-      }
-      auto count = [&](uint32_t t) {
-        int r = 0;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) r += __popcll(__ballot(kk[j] >= t && tid + 64 * j < n));
-        return r;
-      };
-      while (lo < hi) {
-        const uint64_t mid = lo + (hi - lo + 1) / 2;
-        if (count(static_cast<uint32_t>(mid)) >= k) lo = mid; else hi = mid - 1;
-      }
-      c = count(static_cast<uint32_t>(lo));
-    } else {
-      auto count = [&](uint64_t t) {
-        int r = 0;
-        for (int i = tid; i < n; i += 64) r += static_cast<uint32_t>(cand[i] >> 32) >= t ? 1 : 0;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) r += __shfl_xor(r, o);
-        return r;
-      };
-      while (lo < hi) {
-        const uint64_t mid = lo + (hi - lo + 1) / 2;
-        if (count(mid) >= k) lo = mid; else hi = mid - 1;
-      }
-      c = count(lo);
-    }
-    if (tid == 0) {
-      red[0] = lo;
-      red[1] = static_cast<uint64_t>(c);
-    }
-  }
-  __syncthreads();
-  const uint32_t tk0 = static_cast<uint32_t>(red[0]);
-  const int nk0 = static_cast<int>(red[1]);
-  __syncthreads();
-  if (nk0 <= 64) {
-    if (tid < 64) finish_small(a, out, cand, n, tk0, nk0);
-    return;
-  }
-  block_sort_desc(cand, n);
   auto key_at = [&](int i) { return static_cast<uint32_t>(cand[i] >> 32); };
   const float m = key_value(key_at(0));
   // top-k: the first k entries and every later one tied with the k-th (n >= k: the list holds
@@ -374,6 +312,102 @@ __device__ void finish_candidates(const FilterArgs& a, float* out, uint64_t* can
     out[v] = static_cast<float>(static_cast<double>(key_value(static_cast<uint32_t>(e >> 32))) -
                                 static_cast<double>(m) - lse);
   }
+}
+
+// Wavefront 0: moves the nk (<= 64) entries of cand[0, n) with key >= tk to the front, in list
+// order (an entry moves only towards the front, past entries this wavefront has already read).
+__device__ void front_small(uint64_t* cand, int n, uint32_t tk) {
+  const int lane = lane_id();
+  int base = 0;
+  for (int i0 = 0; i0 < n; i0 += 64) {
+    const int i = i0 + lane;
+    const uint64_t c = i < n ? cand[i] : 0;
+    const bool in = i < n && static_cast<uint32_t>(c >> 32) >= tk;
+    const uint64_t msk = __ballot(in);
+    if (in) cand[base + __popcll(msk & ((1ull << lane) - 1))] = c;
+    base += __popcll(msk);
+    asm volatile("" ::: "memory");
+  }
+}
+
+// Sorts a candidate list - visiting keys (key of s, ~id) of every token whose s is at least a
+// lower bound of the row's k-th largest s - in visiting order (s descending, id ascending),
+// applies both cuts and writes the kept tokens' log-probabilities; the rest of the output row
+// already holds -inf. Needs n >= k and n <= kCandCap; all kFT threads call it.
+// `least`: a key that at least k entries of the list reach (0 if none is known).
+__device__ void finish_candidates(const FilterArgs& a, float* out, uint64_t* cand, int n,
+                                  uint64_t* red, double* redd, uint32_t least) {
+  const int tid = threadIdx.x;
+  const int k = static_cast<int>(a.top_k);
+  // Wavefront 0: the k-th largest key of the list (bisection with ballots over the list) and
+  // how many entries are at or above it.
+  if (tid < 64) {
+    uint64_t lo = least, hi = 0xFFFFFFFFu;
+    int c = 0;
+    if (n <= 8 * 64) {  // up to 8 keys per lane, in registers; counts by ballot
+      uint32_t kk[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int i = tid + 64 * j;
+        kk[j] = i < n ? static_cast<uint32_t>(cand[i] >> 32) : 0;
+      }
+      auto count = [&](uint32_t t) {
+        int r = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) r += __popcll(__ballot(kk[j] >= t && tid + 64 * j < n));
+        return r;
+      };
+      uint32_t top = 0;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) top = max(top, kk[j]);
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) top = max(top, static_cast<uint32_t>(__shfl_xor(top, o)));
+      hi = top;
+      while (lo < hi) {
+        const uint64_t mid = lo + (hi - lo + 1) / 2;
+        if (count(static_cast<uint32_t>(mid)) >= k) lo = mid; else hi = mid - 1;
+      }
+      c = count(static_cast<uint32_t>(lo));
+    } else {
+      auto count = [&](uint64_t t) {
+        int r = 0;
+        for (int i = tid; i < n; i += 64) r += static_cast<uint32_t>(cand[i] >> 32) >= t ? 1 : 0;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) r += __shfl_xor(r, o);
+        return r;
+      };
+      while (lo < hi) {
+        const uint64_t mid = lo + (hi - lo + 1) / 2;
+        if (count(mid) >= k) lo = mid; else hi = mid - 1;
+      }
+      c = count(lo);
+    }
+    if (tid == 0) {
+      red[0] = lo;
+      red[1] = static_cast<uint64_t>(c);
+    }
+  }
+  __syncthreads();
+  const uint32_t tk0 = static_cast<uint32_t>(red[0]);
+  const int nk0 = static_cast<int>(red[1]);
+  __syncthreads();
+  if (nk0 <= 64) {
+    if (tid < 64) {
+      front_small(cand, n, tk0);
+      // each lane counts the larger keys (all differ) for its place in visiting order
+      const uint64_t mine = tid < nk0 ? cand[tid] : 0;
+      int rank = 0;
+#pragma unroll 4
+      for (int j = 0; j < nk0; ++j) rank += lane_u64(mine, j) > mine ? 1 : 0;
+      asm volatile("" ::: "memory");
+      if (tid < nk0) cand[rank] = mine;
+      asm volatile("" ::: "memory");
+      finish_small(a, out, tid < nk0 ? cand[tid] : 0, nk0);
+    }
+    return;
+  }
+  block_sort_desc(cand, n);
+  finish_sorted(a, out, cand, n, red, redd);
 }
 
 __device__ bool filter_fast(const FilterArgs& a, const float* in, float* out, bool vec,
@@ -510,7 +544,7 @@ __device__ bool filter_fast(const FilterArgs& a, const float* in, float* out, bo
   const int n = *sh_n;
   __syncthreads();
   if (n > kCandCap) return false;
-  finish_candidates(a, out, cand, n, red, redd, sh_n);
+  finish_candidates(a, out, cand, n, red, redd, 0);
   return true;
 }
 
@@ -669,6 +703,83 @@ constexpr float kNucScale = kNucBins / 27.8f;  // P(v) = 0 below s - m = -40 ln 
 // P(v) >= 1: when the cut's bin is one of them, the later passes need only the bins.
 constexpr int kNucSureBin = 2000;
 
+// The bin where the running mass of a row's bins (b0, b1: this thread's bins 2 tid and 2 tid + 1)
+// reaches T_p = ceil(p Z), the mass before it and T_p. False if the row has no mass (no finite
+// logit). All kFT threads call it; it starts and ends with a barrier.
+__device__ __forceinline__ bool nucleus_crossing(uint64_t b0, uint64_t b1, float top_p,
+                                                 uint64_t* red, int* bstar, uint64_t* before,
+                                                 uint64_t* tp_out) {
+  const int tid = threadIdx.x;
+  const uint64_t loc = b0 + b1;
+  const uint64_t incl = wave_incl_scan_u64(loc);
+  __syncthreads();
+  if (lane_id() == 63) red[tid >> 6] = incl;
+  __syncthreads();
+  uint64_t base = 0, z = 0;
+#pragma unroll
+  for (int w = 0; w < kFW; ++w) {
+    const uint64_t r = red[w];
+    base += w < (tid >> 6) ? r : 0;
+    z += r;
+  }
+  __syncthreads();
+  uint64_t tp = static_cast<uint64_t>(ceil(__dmul_rn(static_cast<double>(top_p),
+                                                     static_cast<double>(z))));
+  if (tp == 0) tp = 1;
+  const uint64_t ex0 = base + incl - loc, ex1 = ex0 + b0;  // mass before bins 2 tid, 2 tid + 1
+  if (ex0 < tp && tp <= ex1) {
+    red[0] = 2 * tid;
+    red[1] = ex0;
+  } else if (ex1 < tp && tp <= ex1 + b1) {
+    red[0] = 2 * tid + 1;
+    red[1] = ex1;
+  }
+  __syncthreads();
+  *bstar = static_cast<int>(red[0]);
+  *before = red[1];
+  *tp_out = tp;
+  __syncthreads();
+  return z > 0;
+}
+
+// Orders the crossing bin's n tokens (0 < n <= kCandCap, `before` the mass of the earlier bins)
+// and takes those whose preceding mass is below T_p: returns the log-normaliser of the kept set,
+// relative to the row's maximum m, and in `cut` the last kept token's visiting key.
+__device__ __forceinline__ double nucleus_kept(uint64_t* cand, int n, float m, uint64_t before,
+                                               uint64_t tp, uint64_t* red, uint64_t* cut) {
+  const int tid = threadIdx.x;
+  block_sort_desc(cand, n);
+  // kept prefix of the bin: four entries per thread in visiting order
+  uint64_t P4[4], l4 = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int i = 4 * tid + j;
+    P4[j] = i < n ? quant_detexp32(__fsub_rn(key_value(static_cast<uint32_t>(cand[i] >> 32)), m)) : 0;
+    l4 += P4[j];
+  }
+  const uint64_t inc4 = wave_incl_scan_u64(l4);
+  if (lane_id() == 63) red[tid >> 6] = inc4;
+  __syncthreads();
+  uint64_t base4 = 0;
+#pragma unroll
+  for (int w = 0; w < kFW; ++w) base4 += w < (tid >> 6) ? red[w] : 0;
+  __syncthreads();
+  uint64_t run = before + base4 + inc4 - l4;
+  uint64_t cnt = 0, kept_mass = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    if (4 * tid + j < n && run < tp) {
+      ++cnt;
+      kept_mass += P4[j];
+    }
+    run += P4[j];
+  }
+  const uint64_t nkeep = block_sum_u64(cnt, red);
+  const uint64_t kmass = before + block_sum_u64(kept_mass, red);
+  *cut = cand[nkeep - 1];
+  return log(static_cast<double>(kmass)) - 40.0 * 0.6931471805599453;
+}
+
 __device__ bool filter_nucleus(const FilterArgs& a, const float* in, float* out, bool vec,
                                uint64_t* bins, uint64_t* cand, uint64_t* red, int* sh_n) {
   const int tid = threadIdx.x;
@@ -702,36 +813,12 @@ __device__ bool filter_nucleus(const FilterArgs& a, const float* in, float* out,
     if (P) atomicAdd(reinterpret_cast<unsigned long long*>(&bins[b]), static_cast<unsigned long long>(P));
   });
   __syncthreads();
-  // the crossing bin: exclusive prefix of the bin masses (two bins per thread)
-  const uint64_t b0 = bins[2 * tid], b1 = bins[2 * tid + 1];
-  const uint64_t loc = b0 + b1;
-  const uint64_t incl = wave_incl_scan_u64(loc);
-  if (lane_id() == 63) red[tid >> 6] = incl;
-  __syncthreads();
-  uint64_t base = 0, z = 0;
-#pragma unroll
-  for (int w = 0; w < kFW; ++w) {
-    const uint64_t r = red[w];
-    base += w < (tid >> 6) ? r : 0;
-    z += r;
-  }
-  __syncthreads();
-  uint64_t tp = static_cast<uint64_t>(ceil(__dmul_rn(static_cast<double>(a.top_p),
-                                                     static_cast<double>(z))));
-  if (tp == 0) tp = 1;
-  const uint64_t ex0 = base + incl - loc, ex1 = ex0 + b0;  // mass before bins 2 tid, 2 tid + 1
-  if (ex0 < tp && tp <= ex1) {
-    red[0] = 2 * tid;
-    red[1] = ex0;
-  } else if (ex1 < tp && tp <= ex1 + b1) {
-    red[0] = 2 * tid + 1;
-    red[1] = ex1;
-  }
   if (tid == 0) *sh_n = 0;
+  const uint64_t b0 = bins[2 * tid], b1 = bins[2 * tid + 1];
   __syncthreads();
-  const int bstar = static_cast<int>(red[0]);
-  const uint64_t before = red[1];
-  __syncthreads();
+  int bstar;
+  uint64_t before, tp;
+  if (!nucleus_crossing(b0, b1, a.top_p, red, &bstar, &before, &tp)) return false;
   auto bin_of = [&](float sv) {
     return min(kNucBins - 1, static_cast<int>(__fmul_rn(-__fsub_rn(sv, m), kNucScale)));
   };
@@ -757,36 +844,8 @@ __device__ bool filter_nucleus(const FilterArgs& a, const float* in, float* out,
   const int n = *sh_n;
   __syncthreads();
   if (n > kCandCap) return false;
-  block_sort_desc(cand, n);
-  // kept prefix of the bin: four entries per thread in visiting order
-  uint64_t P4[4], l4 = 0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int i = 4 * tid + j;
-    P4[j] = i < n ? quant_detexp32(__fsub_rn(key_value(static_cast<uint32_t>(cand[i] >> 32)), m)) : 0;
-    l4 += P4[j];
-  }
-  const uint64_t inc4 = wave_incl_scan_u64(l4);
-  if (lane_id() == 63) red[tid >> 6] = inc4;
-  __syncthreads();
-  uint64_t base4 = 0;
-#pragma unroll
-  for (int w = 0; w < kFW; ++w) base4 += w < (tid >> 6) ? red[w] : 0;
-  __syncthreads();
-  uint64_t run = before + base4 + inc4 - l4;
-  uint64_t cnt = 0, kept_mass = 0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    if (4 * tid + j < n && run < tp) {
-      ++cnt;
-      kept_mass += P4[j];
-    }
-    run += P4[j];
-  }
-  const uint64_t nkeep = block_sum_u64(cnt, red);
-  const uint64_t kmass = before + block_sum_u64(kept_mass, red);
-  const uint64_t cut = cand[nkeep - 1];
-  const double lse = log(static_cast<double>(kmass)) - 40.0 * 0.6931471805599453;
+  uint64_t cut;
+  const double lse = nucleus_kept(cand, n, m, before, tp, red, &cut);
   // 4. output row
   if (sure) {
     scan([&](int64_t v, float sv) {
@@ -807,12 +866,741 @@ __device__ bool filter_nucleus(const FilterArgs& a, const float* in, float* out,
   return true;
 }
 
+// Rows with the nucleus alone (T > 0, top_k off, p < 1): the binned path, or the general one
+// when the cut's bin is too crowded.
+__global__ __launch_bounds__(kFT) void filter_nucleus_kernel(FilterArgs a) {
+  __shared__ uint64_t hist[256];
+  __shared__ uint64_t nbins[kNucBins];
+  __shared__ uint64_t cand[kCandCap];
+  __shared__ int sh_n;
+  __shared__ uint64_t red[kFW];
+  __shared__ double redd[kFW];
+  __shared__ uint32_t sh_digit;
+  __shared__ uint64_t sh_above;
+  const int64_t n = blockIdx.x;
+  const int64_t V = a.V;
+  const float* in = a.logits + n * V;
+  float* out = a.logp + n * V;
+  const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(in) & 15) == 0 &&
+                   (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+  if (filter_nucleus(a, in, out, vec, nbins, cand, red, &sh_n)) return;
+  filter_general(a, in, out, vec, hist, red, redd, &sh_digit, &sh_above);
+}
+
+// ---------------------------------------------------------------------------------------
+// Rows split over several workgroups (T > 0, V >= kSplitMinV, with a workspace): one workgroup
+// per row leaves most of the chip idle for the rows of a few sequences and, with four passes over
+// the row each bound by one CU, ran 272 nucleus rows of 151,936 logits in 286 us; with every pass
+// split they are bound by the passes' traffic. A row is read in 16-byte groups at any alignment
+// of its start (global vector loads need 4-byte alignment only); the groups past V are masked.
+// ---------------------------------------------------------------------------------------
+constexpr int64_t kSplitMinV = 16384;  // two segments; below, one workgroup covers the row at once
+// The nucleus alone takes six launches when split, and from 32,768 ids (one mass part) they pay:
+// 300 rows 76 -> 69 us, 16 rows 36 -> 34 us, where 300 rows of 20,000 ids took 62 us split against 53.
+constexpr int64_t kSplitMinNucleus = 32768;
+
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+
+// The TH * U groups of four logits that a workgroup of TH threads holds from element e0 of the
+// row on: thread t has groups t, t + TH, ...; elements past V read as -inf.
+template <int TH, int U>
+__device__ __forceinline__ void load_groups(const float* in, int64_t V, int64_t e0, int tid,
+                                            float (&x)[U][4]) {
+  if (e0 + 4 * TH * U <= V) {
+    f32x4u g[U];
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+      g[i] = *reinterpret_cast<const f32x4u*>(in + e0 + 4 * (tid + i * TH));
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) x[i][q] = g[i][q];
+  } else {
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int64_t v = e0 + 4 * (tid + i * TH) + q;
+        x[i][q] = v < V ? in[v] : -INFINITY;
+      }
+  }
+}
+
+template <int TH, int U>
+__device__ __forceinline__ void store_groups(float* out, int64_t V, int64_t e0, int tid,
+                                             const float (&x)[U][4]) {
+  if (e0 + 4 * TH * U <= V) {
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+      *reinterpret_cast<f32x4u*>(out + e0 + 4 * (tid + i * TH)) =
+          f32x4u{x[i][0], x[i][1], x[i][2], x[i][3]};
+  } else {
+#pragma unroll
+    for (int i = 0; i < U; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int64_t v = e0 + 4 * (tid + i * TH) + q;
+        if (v < V) out[v] = x[i][q];
+      }
+  }
+}
+
+// A segment: the 8192 elements that 256 threads hold in registers.
+constexpr int kSegT = 256;
+constexpr int kSegU = 8;
+constexpr int kSegElems = 4 * kSegT * kSegU;
+static_assert((int64_t{1} << 24) / kSegElems * 16 <= kFilterRowBytes, "segment results of a row");
+
+__host__ __device__ constexpr int64_t n_segs(int64_t V) { return (V + kSegElems - 1) / kSegElems; }
+
+// Largest key of a 256-thread group (threads 256 g .. 256 g + 255); `red` holds 4 words per group.
+// Every thread of the workgroup calls it.
+__device__ __forceinline__ uint32_t group_max_u32(uint32_t v, uint32_t* red, int grp) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v = max(v, static_cast<uint32_t>(__shfl_xor(v, o)));
+  if (lane_id() == 0) red[4 * grp + ((threadIdx.x >> 6) & 3)] = v;
+  __syncthreads();
+  const uint32_t m = max(max(red[4 * grp], red[4 * grp + 1]), max(red[4 * grp + 2], red[4 * grp + 3]));
+  __syncthreads();
+  return m;
+}
+
+// e^x for x <= 0 to 2^-32 relative: Cody-Waite reduction and the Taylor polynomial of degree 8 in
+// binary64 (0.3466^9 / 9! < 2^-32), for sums whose result is rounded to binary32. 0 for -inf, NaN
+// and below -708.
+__device__ __forceinline__ double exp_sum(double x) {
+  const double n = rint(x * 0x1.71547652b82fep+0);
+  const double r = fma(n, -0x1.62e42fefa39efp-1, x);
+  double p = 1.0 / 40320.0;
+  p = fma(p, r, 1.0 / 5040.0);
+  p = fma(p, r, 1.0 / 720.0);
+  p = fma(p, r, 1.0 / 120.0);
+  p = fma(p, r, 1.0 / 24.0);
+  p = fma(p, r, 1.0 / 6.0);
+  p = fma(p, r, 0.5);
+  p = fma(p, r, 1.0);
+  p = fma(p, r, 1.0);
+  return x > -708.0 ? ldexp(p, static_cast<int>(n)) : 0.0;
+}
+
+// Maximum m of s and sum of exp(s - m) of one segment, by a group of 256 threads (group grp of
+// the workgroup; every thread calls it): the same order of operations whichever kernel runs it.
+struct SegStat {
+  float m;
+  float pad;
+  double sum;
+};
+
+__device__ __forceinline__ SegStat seg_stat(const float* in, int64_t V, int64_t seg, bool live,
+                                            float T, int grp, uint32_t* red, double* redd) {
+  const int t = threadIdx.x & (kSegT - 1);
+  float x[kSegU][4];
+  // a group without a segment takes part with an empty one
+  load_groups<kSegT, kSegU>(in, live ? V : 0, live ? seg * kSegElems : 0, t, x);
+  uint32_t mk = 0;
+#pragma unroll
+  for (int i = 0; i < kSegU; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) mk = max(mk, order_key(x[i][q]));
+  const float m = __fdiv_rn(key_value(group_max_u32(mk, red, grp)), T);
+  const int64_t left = live ? V - seg * kSegElems : 0;  // groups of four past V add nothing
+  double s = 0.0;
+  auto all = [&](auto scale) {
+#pragma unroll
+    for (int i = 0; i < kSegU; ++i)
+      if (4 * kSegT * i < left)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          s += exp_sum(static_cast<double>(scale(x[i][q])) - static_cast<double>(m));
+  };
+  // Quotient's short form where no logit that counts is out of its range: a dividend below 2^-100
+  // changes its term by less than 2^-80 of it, an infinite one has term 0 as its NaN has here.
+  const Quotient div(T);
+  if (div.short_form && fabsf(m) < 0x1p80f)
+    all([&](float v) { return div.quick(v); });
+  else
+    all([&](float v) { return __fdiv_rn(v, T); });
+  s = wave_sum_f64(s);
+  if (lane_id() == 0) redd[4 * grp + ((threadIdx.x >> 6) & 3)] = s;
+  __syncthreads();
+  const double sum = (redd[4 * grp] + redd[4 * grp + 1]) + (redd[4 * grp + 2] + redd[4 * grp + 3]);
+  __syncthreads();
+  return SegStat{m, 0.0f, sum};
+}
+
+// The row's maximum and log-normaliser from its segments' statistics; every wavefront computes
+// the same.
+__device__ __forceinline__ void merge_stats(const SegStat* st, int n, float* m, double* lse) {
+  const int lane = lane_id();
+  float mx = -INFINITY;
+  bool nan = false;
+  for (int i = lane; i < n; i += 64) {
+    nan = nan || st[i].m != st[i].m;
+    mx = fmaxf(mx, st[i].m);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+  if (__ballot(nan)) mx = NAN;  // a NaN logit is the row's maximum in key order
+  double s = 0.0;
+  for (int i = lane; i < n; i += 64)
+    s += st[i].sum * exp(static_cast<double>(st[i].m) - static_cast<double>(mx));
+  *m = mx;
+  *lse = log(wave_sum_f64(s));
+}
+
+__device__ __forceinline__ float log_prob(float sv, float m, double lse) {
+  return static_cast<float>(static_cast<double>(sv) - static_cast<double>(m) - lse);
+}
+
+// Temperature alone, split: statistics per segment, then the output. Two reads and one write of
+// the row, bound by that traffic and the exponentials: 272 rows of 151,936 logits 96 us, 16 rows
+// 14 us, where one workgroup per row with three reads took 251 and 115.
+__global__ __launch_bounds__(kSegT) void filter_stats_kernel(FilterArgs a, int segs) {
+  __shared__ uint32_t red[4];
+  __shared__ double redd[4];
+  const int64_t row = blockIdx.x / segs, seg = blockIdx.x % segs;
+  const SegStat st = seg_stat(a.logits + row * a.V, a.V, seg, true, a.temperature, 0, red, redd);
+  if (threadIdx.x == 0)
+    reinterpret_cast<SegStat*>(a.row_ws + row * kFilterRowBytes)[seg] = st;
+}
+
+__global__ __launch_bounds__(kSegT) void filter_scale_kernel(FilterArgs a, int segs) {
+  const int64_t row = blockIdx.x / segs, seg = blockIdx.x % segs;
+  float x[kSegU][4];
+  load_groups<kSegT, kSegU>(a.logits + row * a.V, a.V, seg * kSegElems, threadIdx.x, x);
+  float m;
+  double lse;
+  merge_stats(reinterpret_cast<const SegStat*>(a.row_ws + row * kFilterRowBytes), segs, &m, &lse);
+#pragma unroll
+  for (int i = 0; i < kSegU; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) x[i][q] = log_prob(__fdiv_rn(x[i][q], a.temperature), m, lse);
+  store_groups<kSegT, kSegU>(a.logp + row * a.V, a.V, seg * kSegElems, threadIdx.x, x);
+}
+
+// Temperature alone, rows of up to two segments: one 256-thread workgroup per row with the same
+// arithmetic, eight to a CU (1000 rows of 3000 ids: 13 us, against 34 with the 1024-thread form
+// below, of which a CU holds one; at 16,384 ids 300 rows take 18 us and one row 12, split 17 and 14).
+constexpr int kRowSegs = 2;
+__global__ __launch_bounds__(kSegT) void filter_scale_rows_kernel(FilterArgs a, int segs) {
+  __shared__ uint32_t red[4];
+  __shared__ double redd[4];
+  __shared__ SegStat st[kRowSegs];
+  const float* in = a.logits + blockIdx.x * a.V;
+  float* out = a.logp + blockIdx.x * a.V;
+  for (int seg = 0; seg < segs; ++seg) {
+    const SegStat s = seg_stat(in, a.V, seg, true, a.temperature, 0, red, redd);
+    if (threadIdx.x == 0) st[seg] = s;
+  }
+  __syncthreads();
+  float m;
+  double lse;
+  merge_stats(st, segs, &m, &lse);
+  for (int64_t e0 = 0; e0 < a.V; e0 += 8 * kSegT) {
+    float x[2][4];
+    load_groups<kSegT, 2>(in, a.V, e0, threadIdx.x, x);
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) x[i][q] = log_prob(__fdiv_rn(x[i][q], a.temperature), m, lse);
+    store_groups<kSegT, 2>(out, a.V, e0, threadIdx.x, x);
+  }
+}
+
+// Temperature alone, one workgroup per row: its four groups take the segments in turn, with the
+// split form's arithmetic, so both give the same bits. `st` holds n_segs(V) statistics.
+__device__ void filter_scale_row(const FilterArgs& a, const float* in, float* out, SegStat* st,
+                                 uint32_t* red, double* redd) {
+  const int grp = threadIdx.x / kSegT;
+  const int n = static_cast<int>(n_segs(a.V));
+  for (int s0 = 0; s0 < n; s0 += kFT / kSegT) {
+    const int seg = s0 + grp;
+    const SegStat s = seg_stat(in, a.V, seg, seg < n, a.temperature, grp, red, redd);
+    if (seg < n && threadIdx.x % kSegT == 0) st[seg] = s;
+  }
+  __syncthreads();
+  float m;
+  double lse;
+  merge_stats(st, n, &m, &lse);
+  for (int64_t e0 = 0; e0 < a.V; e0 += 16 * kFT) {
+    float x[4][4];
+    load_groups<kFT, 4>(in, a.V, e0, threadIdx.x, x);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) x[i][q] = log_prob(__fdiv_rn(x[i][q], a.temperature), m, lse);
+    store_groups<kFT, 4>(out, a.V, e0, threadIdx.x, x);
+  }
+}
+
+// Least key k with ok(k), for a predicate that holds from some key on (and at +inf): 64 probes
+// per step, one per lane; every wavefront computes it.
+template <class F>
+__device__ __forceinline__ uint32_t least_key(F ok) {
+  if (ok(kKeyNegInf)) return kKeyNegInf;
+  uint32_t lo = kKeyNegInf, hi = kKeyPosInf;  // ok(lo) false, ok(hi) true
+  while (hi - lo > 1) {
+    const uint32_t step = (hi - lo + 63) / 64;
+    const uint64_t at = static_cast<uint64_t>(lo) + static_cast<uint64_t>(lane_id() + 1) * step;
+    const uint32_t probe = at < hi ? static_cast<uint32_t>(at) : hi;
+    const uint64_t hit = __ballot(probe == hi || ok(probe));
+    const int f = __ffsll(static_cast<unsigned long long>(hit)) - 1;  // the last lane's probe is hi
+    const uint32_t nhi = static_cast<uint32_t>(__shfl(static_cast<int>(probe), f));
+    if (f > 0) lo = static_cast<uint32_t>(__shfl(static_cast<int>(probe), f - 1));
+    hi = nhi;
+  }
+  return hi;
+}
+
+// Top-k, split (0 < k <= 256): every segment workgroup streams its share of the row once, writing
+// -inf and keeping each thread's largest logit key, and takes the k-th largest of its 512 thread
+// maxima as a lower bound of its share's k-th largest: about k (1 + k / 1024) tokens of the share
+// reach it, where bounds from parts of the share let through several times as many. The threads
+// that hold such tokens read their groups again (from L2) and append them to the share's list in
+// the workspace, headed by the bound, the count and the share's j-th largest thread maximum,
+// j = ceil(k / shares). A merge workgroup per row keeps the tokens that reach the largest of the
+// shares' bounds and the least of their j-th largest (j tokens of every share reach that one, so
+// the row's k-th largest does): two or three times k of them, selects among them and finishes.
+// 16 rows of 151,936 at k = 50: 11.5 + 7.1 us, against 23 + 54 us with 4 shares per row, bounds per
+// wavefront and a merge that bisected 1,600 candidates; 272 rows at k = 20 84 us (112). A list
+// that overflows, or no share with a bound, sends the row to the general path.
+// 16 shares per row up to k = 128, 8 above: k tokens per share and the overshoot stay within a
+// share's list, and the smallest row (kSplitMinV) still has more non-empty threads than k.
+constexpr int kTopThreads = 512;
+constexpr int kTopEntries = kFilterRowBytes / 8;  // over all shares of a row, two heads each included
+__host__ __device__ constexpr int top_shares(int64_t k) { return k <= 128 ? 16 : 8; }
+static_assert(kSplitMinV / 4 / top_shares(128) >= 128 && kSplitMinV / 4 / top_shares(256) >= 256,
+              "at least k non-empty threads per share");
+
+__global__ __launch_bounds__(kTopThreads) void filter_topk_share_kernel(FilterArgs a, int shares) {
+  __shared__ int s_bin[3][kTopThreads];
+  __shared__ int s_wave[2][kTopThreads / 64];
+  __shared__ int s_pick[2][2];
+  static_assert(kTopThreads == 512, "one histogram bin per thread");
+  __shared__ int sh_n;
+  const int64_t row = blockIdx.x / shares;
+  const int share = static_cast<int>(blockIdx.x % shares);
+  const int tid = threadIdx.x;
+  const int64_t V = a.V;
+  const float T = a.temperature;
+  const int k = static_cast<int>(a.top_k);
+  const int cap = kTopEntries / shares - 2;
+  const float* in = a.logits + row * V;
+  float* out = a.logp + row * V;
+  // This share's groups of four: [g0, g1); thread t has g0 + t, g0 + t + 512, ...
+  const int64_t groups = (V + 3) / 4;
+  const int64_t per = (groups + shares - 1) / shares;
+  const int64_t g0 = min(groups, share * per), g1 = min(groups, g0 + per);
+  const int64_t gfull = min(g1, V / 4);  // groups of four within V
+  uint32_t top = 0;
+  auto see = [&](float x) { top = max(top, order_key(x)); };
+  const f32x4u ninf = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+  int64_t j = g0 + tid;
+  for (; j + (kBatch - 1) * kTopThreads < gfull; j += kBatch * kTopThreads) {
+    f32x4u x[kBatch];
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u)
+      x[u] = *reinterpret_cast<const f32x4u*>(in + 4 * (j + u * kTopThreads));
+#pragma unroll
+    for (int u = 0; u < kBatch; ++u) {
+      *reinterpret_cast<f32x4u*>(out + 4 * (j + u * kTopThreads)) = ninf;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) see(x[u][q]);
+    }
+  }
+#pragma unroll 4
+  for (; j < gfull; j += kTopThreads) {
+    const f32x4u x = *reinterpret_cast<const f32x4u*>(in + 4 * j);
+    *reinterpret_cast<f32x4u*>(out + 4 * j) = ninf;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) see(x[q]);
+  }
+  if (j < g1)  // the row's last, partial group
+    for (int64_t v = 4 * j; v < V; ++v) {
+      see(in[v]);
+      out[v] = -INFINITY;
+    }
+  // Lower bounds of the share's k-th and j-th largest logit keys: those of its thread maxima, to 18
+  // bits of the key, by two levels of 512-bin histograms (thread t counts from the top: bin 511 - t).
+  const int need[2] = {k, (k + shares - 1) / shares};
+  s_bin[0][tid] = 0;
+  s_bin[1][tid] = 0;
+  s_bin[2][tid] = 0;
+  if (tid == 0) sh_n = 0;
+  __syncthreads();
+  atomicAdd(&s_bin[2][top >> 23], 1);
+  __syncthreads();
+  auto pick = [&](const int* bins, int n, int q) {  // the bin the n-th from the top is in
+    const int c = bins[kTopThreads - 1 - tid];
+    int upto = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int t = __shfl_up(upto, o);
+      if (lane_id() >= o) upto += t;
+    }
+    if (lane_id() == 63) s_wave[q][tid >> 6] = upto;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kTopThreads / 64; ++w) upto += w < (tid >> 6) ? s_wave[q][w] : 0;
+    if (upto >= n && upto - c < n) {
+      s_pick[q][0] = kTopThreads - 1 - tid;
+      s_pick[q][1] = n - (upto - c);  // its place in the bin
+    }
+  };
+  pick(s_bin[2], need[0], 0);
+  pick(s_bin[2], need[1], 1);
+  __syncthreads();
+  const uint32_t b0 = s_pick[0][0], b1 = s_pick[1][0];
+  const int n0 = s_pick[0][1], n1 = s_pick[1][1];
+  if ((top >> 23) == b0) atomicAdd(&s_bin[0][(top >> 14) & 511], 1);
+  if ((top >> 23) == b1) atomicAdd(&s_bin[1][(top >> 14) & 511], 1);
+  __syncthreads();
+  pick(s_bin[0], n0, 0);
+  pick(s_bin[1], n1, 1);
+  __syncthreads();
+  const uint32_t lo = (b0 << 23) | (static_cast<uint32_t>(s_pick[0][0]) << 14);
+  const uint32_t jth = (b1 << 23) | (static_cast<uint32_t>(s_pick[1][0]) << 14);
+  // A share with fewer than k threads holding a logit above -inf (a masked part of the vocabulary)
+  // lists all of those and gives no bound.
+  const bool bound = lo > kKeyNegInf;
+  const uint32_t s_low = bound ? order_key(__fdiv_rn(key_value(lo), T)) : 0;
+  uint32_t x_low = kKeyNegInf + 1;
+  if (bound) {  // the least logit key with that s: almost always within 64 of the bound's
+    auto reaches = [&](uint32_t q) { return order_key(__fdiv_rn(key_value(q), T)) >= s_low; };
+    const uint64_t hit = lo > kKeyNegInf + 64 ? __ballot(reaches(lo - 63 + lane_id())) : 1;
+    x_low = (hit & 1) ? least_key(reaches)
+                      : lo - 64 + static_cast<uint32_t>(__ffsll(static_cast<unsigned long long>(hit)));
+  }
+  uint64_t* list = reinterpret_cast<uint64_t*>(a.row_ws + row * kFilterRowBytes) +
+                   static_cast<int64_t>(share) * (cap + 2);
+  auto take = [&](int64_t v, float x) {
+    if (order_key(x) >= x_low) {
+      const int slot = atomicAdd(&sh_n, 1);
+      if (slot < cap) list[2 + slot] = visit_key(order_key(__fdiv_rn(x, T)), v);
+    }
+  };
+  if (top >= x_low) {
+    int64_t i = g0 + tid;
+#pragma unroll 4
+    for (; i < gfull; i += kTopThreads) {
+      const f32x4u x = *reinterpret_cast<const f32x4u*>(in + 4 * i);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) take(4 * i + q, x[q]);
+    }
+    if (i < g1)
+      for (int64_t v = 4 * i; v < V; ++v) take(v, in[v]);
+  }
+  __syncthreads();
+  if (tid == 0) {
+    list[0] = (static_cast<uint64_t>(s_low) << 32) | static_cast<uint32_t>(sh_n);
+    list[1] = jth > kKeyNegInf ? order_key(__fdiv_rn(key_value(jth), T)) : 0;
+  }
+}
+
+__global__ __launch_bounds__(kFT) void filter_topk_merge_kernel(FilterArgs a, int shares) {
+  __shared__ uint64_t hist[256];
+  __shared__ uint64_t cand[kCandCap];
+  __shared__ int sh_n;
+  __shared__ uint64_t red[kFW];
+  __shared__ double redd[kFW];
+  __shared__ uint32_t sh_digit;
+  __shared__ uint64_t sh_above;
+  static_assert(kCandCap >= kTopEntries, "every list entry of a row fits");
+  const int64_t row = blockIdx.x;
+  const int64_t V = a.V;
+  const int tid = threadIdx.x;
+  const float* in = a.logits + row * V;
+  float* out = a.logp + row * V;
+  const uint64_t* lists = reinterpret_cast<const uint64_t*>(a.row_ws + row * kFilterRowBytes);
+  const int per = kTopEntries / shares;
+  // entries tid, tid + kFT, ... of the lists, loaded with the heads (unwritten ones are not used)
+  uint64_t e[kTopEntries / kFT];
+#pragma unroll
+  for (int i = 0; i < kTopEntries / kFT; ++i) e[i] = lists[tid + i * kFT];
+  const uint64_t head = lists[(lane_id() % shares) * per];
+  uint32_t kth = static_cast<uint32_t>(head >> 32);
+  uint32_t jth = static_cast<uint32_t>(lists[(lane_id() % shares) * per + 1]);
+  const bool over = __ballot(static_cast<int>(static_cast<uint32_t>(head)) > per - 2) != 0;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    kth = max(kth, static_cast<uint32_t>(__shfl_xor(kth, o)));
+    jth = min(jth, static_cast<uint32_t>(__shfl_xor(jth, o)));
+  }
+  const uint32_t least = max(kth, jth);
+  if (over || least == 0) {
+    const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(in) & 15) == 0 &&
+                     (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+    filter_general(a, in, out, vec, hist, red, redd, &sh_digit, &sh_above);
+    return;
+  }
+  if (tid == 0) sh_n = 0;
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < kTopEntries / kFT; ++i) {
+    const int at = tid + i * kFT, share = at / per, slot = at % per;
+    const int cnt = static_cast<int>(static_cast<uint32_t>(__shfl(head, share)));
+    if (slot > 1 && slot < 2 + cnt && static_cast<uint32_t>(e[i] >> 32) >= least)
+      cand[atomicAdd(&sh_n, 1)] = e[i];
+  }
+  __syncthreads();
+  const int n = sh_n;
+  block_sort_desc(cand, n);
+  // the tokens at or above the k-th largest s: at most 64 of them finish in wavefront 0
+  const uint32_t tk = static_cast<uint32_t>(cand[a.top_k - 1] >> 32);
+  if (n <= 64 || static_cast<uint32_t>(cand[64] >> 32) < tk) {
+    if (tid < 64) {
+      const uint64_t c = tid < n ? cand[tid] : 0;
+      const bool in = tid < n && static_cast<uint32_t>(c >> 32) >= tk;
+      finish_small(a, out, in ? c : 0, __popcll(__ballot(in)));
+    }
+    return;
+  }
+  finish_sorted(a, out, cand, n, red, redd);
+}
+
+// Nucleus alone, split: the same integer decisions as filter_nucleus in six launches.
+//   1. max      largest logit key per segment (and the row's bins cleared);
+//   2. mass     integer mass per bin: 32,768 ids per workgroup in LDS bins, whose non-empty ones
+//               are added to the row's bins (integer sums: any order gives the same);
+//   3. edge     one workgroup per row: the crossing bin, and its ends as logits (bins are
+//               non-increasing in the logit, so a bin is an interval of logits);
+//   4. gather   the crossing bin's tokens appended to the row's list: the row is read again with two
+//               compares per id;
+//   5. cut      one workgroup per row: the list's order, the cut and the normaliser;
+//   6. write    kept ids by comparing logit keys, so only kept ids are divided.
+// The mass pass is bound by its arithmetic (about 50 lane instructions per id for the contract's
+// division and quantised exponential), the others by the row's traffic. 272 rows of 151,936
+// logits at T = 0.7: 27 + 54 + 8 + 25 + 13 + 53 us (189 us per call, 294 with one workgroup per
+// row); 16 rows 41 us (123).
+struct NucleusRow {  // a row's workspace: this, seg_max[segs], then the list
+  uint64_t bins[kNucBins];
+  uint64_t before, tp;
+  double lse;
+  float m;
+  float edge[2];  // the crossing bin's logits: [edge[0], edge[1])
+  int sure;       // every token of the bin has positive mass
+  int count;      // tokens listed
+  int live;       // the row has mass
+};
+constexpr int64_t kNucMaxSegs = (int64_t{1} << 24) / kSegElems;
+static_assert(sizeof(NucleusRow) % 8 == 0 &&
+                  sizeof(NucleusRow) + 4 * kNucMaxSegs + 8 <= kFilterRowBytes,
+              "a row's workspace");
+constexpr int kMassU = 8;
+constexpr int kMassElems = 4 * kFT * kMassU;
+
+__device__ __forceinline__ NucleusRow* nucleus_row(const FilterArgs& a, int64_t row) {
+  return reinterpret_cast<NucleusRow*>(a.row_ws + row * kFilterRowBytes);
+}
+__device__ __forceinline__ uint32_t* nucleus_seg_max(NucleusRow* w) {
+  return reinterpret_cast<uint32_t*>(w + 1);
+}
+__device__ __forceinline__ uint64_t* nucleus_list(NucleusRow* w, int segs) {
+  return reinterpret_cast<uint64_t*>(w + 1) + (segs + 1) / 2;
+}
+__device__ __forceinline__ int nucleus_cap(int segs) {  // entries of the list, about 2,030
+  return min(kCandCap, static_cast<int>((kFilterRowBytes - sizeof(NucleusRow)) / 8) - (segs + 1) / 2);
+}
+
+// s of the row's largest logit, from the segments' keys; every wavefront computes it.
+__device__ __forceinline__ float nucleus_max(NucleusRow* w, int segs, float T) {
+  uint32_t k = 0;
+  for (int i = lane_id(); i < segs; i += 64) k = max(k, nucleus_seg_max(w)[i]);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) k = max(k, static_cast<uint32_t>(__shfl_xor(k, o)));
+  return __fdiv_rn(key_value(k), T);
+}
+
+__global__ __launch_bounds__(kSegT) void nucleus_max_kernel(FilterArgs a, int segs) {
+  __shared__ uint32_t red[4];
+  const int64_t row = blockIdx.x / segs, seg = blockIdx.x % segs;
+  NucleusRow* w = nucleus_row(a, row);
+  float x[kSegU][4];
+  load_groups<kSegT, kSegU>(a.logits + row * a.V, a.V, seg * kSegElems, threadIdx.x, x);
+  if (seg == 0)
+    for (int i = threadIdx.x; i < kNucBins; i += kSegT) w->bins[i] = 0;
+  uint32_t k = 0;
+#pragma unroll
+  for (int i = 0; i < kSegU; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) k = max(k, order_key(x[i][q]));
+  k = group_max_u32(k, red, 0);
+  if (threadIdx.x == 0) nucleus_seg_max(w)[seg] = k;
+}
+
+__global__ __launch_bounds__(kFT) void nucleus_mass_kernel(FilterArgs a, int parts, int segs) {
+  __shared__ uint64_t bins[kNucBins];
+  const int64_t row = blockIdx.x / parts, part = blockIdx.x % parts;
+  NucleusRow* w = nucleus_row(a, row);
+  const float T = a.temperature;
+  float x[kMassU][4];
+  load_groups<kFT, kMassU>(a.logits + row * a.V, a.V, part * kMassElems, threadIdx.x, x);
+  const float m = nucleus_max(w, segs, T);
+  for (int i = threadIdx.x; i < kNucBins; i += kFT) bins[i] = 0;
+  __syncthreads();
+  auto add = [&](float sv) {
+    const float d = __fsub_rn(sv, m);
+    const uint64_t P = quant_detexp32(d);
+    const int b = min(kNucBins - 1, static_cast<int>(__fmul_rn(-d, kNucScale)));
+    if (P) atomicAdd(reinterpret_cast<unsigned long long*>(&bins[b]),
+                     static_cast<unsigned long long>(P));
+  };
+  auto all = [&](auto scale) {
+#pragma unroll
+    for (int i = 0; i < kMassU; ++i)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) add(scale(x[i][q]));
+  };
+  // Quotient's short form needs |x| >= 2^-100 (or 0, or an infinity, whose NaN has mass 0 as
+  // -inf must); a smaller logit's s is below 2^-79, where its last bit cannot change s - m once
+  // |m| >= 2^-50.
+  const Quotient div(T);
+  if (T == 1.0f)
+    all([](float v) { return v; });
+  else if (div.short_form && fabsf(m) >= 0x1p-50f)
+    all([&](float v) { return div.quick(v); });
+  else
+    all([&](float v) { return __fdiv_rn(v, T); });
+  __syncthreads();
+  for (int i = threadIdx.x; i < kNucBins; i += kFT)
+    if (bins[i]) atomicAdd(reinterpret_cast<unsigned long long*>(&w->bins[i]),
+                           static_cast<unsigned long long>(bins[i]));
+}
+
+__global__ __launch_bounds__(kFT) void nucleus_edge_kernel(FilterArgs a, int segs) {
+  __shared__ uint64_t red[kFW];
+  const int64_t row = blockIdx.x;
+  const int tid = threadIdx.x;
+  const float T = a.temperature;
+  NucleusRow* w = nucleus_row(a, row);
+  const uint64_t m0 = w->bins[2 * tid], m1 = w->bins[2 * tid + 1];
+  const float m = nucleus_max(w, segs, T);
+  int bstar;
+  uint64_t before, tp;
+  const bool live = nucleus_crossing(m0, m1, a.top_p, red, &bstar, &before, &tp);
+  if (tid < 128) {  // the ends of the crossing bin, one per wavefront
+    const int below = bstar - (tid >> 6);
+    const uint32_t k = least_key([&](uint32_t q) {
+      const float d = __fsub_rn(__fdiv_rn(key_value(q), T), m);
+      return min(kNucBins - 1, static_cast<int>(__fmul_rn(-d, kNucScale))) <= below;
+    });
+    if (lane_id() == 0) w->edge[tid >> 6] = key_value(k);
+  }
+  if (tid == 0) {
+    w->before = before;
+    w->tp = tp;
+    w->m = m;
+    w->sure = bstar <= kNucSureBin;
+    w->count = 0;
+    w->live = live;
+  }
+}
+
+__global__ __launch_bounds__(kSegT) void nucleus_gather_kernel(FilterArgs a, int segs) {
+  const int64_t row = blockIdx.x / segs, seg = blockIdx.x % segs;
+  const float* in = a.logits + row * a.V;
+  NucleusRow* w = nucleus_row(a, row);
+  float x[kSegU][4];
+  load_groups<kSegT, kSegU>(in, a.V, seg * kSegElems, threadIdx.x, x);
+  if (!w->live) return;
+  const float lo = w->edge[0], hi = w->edge[1];
+  uint32_t hit = 0;
+#pragma unroll
+  for (int i = 0; i < kSegU; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) hit |= x[i][q] >= lo && x[i][q] < hi ? 1u << (4 * i + q) : 0;
+  uint64_t* list = nucleus_list(w, segs);
+  const int cap = nucleus_cap(segs);
+  while (hit) {  // few: read again rather than picked out of the registers
+    const int at = __ffs(static_cast<int>(hit)) - 1;
+    hit &= hit - 1;
+    const int64_t v = seg * kSegElems + 4 * (static_cast<int>(threadIdx.x) + (at >> 2) * kSegT) + (at & 3);
+    if (v >= a.V) continue;  // a masked place of the last segment
+    const float sv = __fdiv_rn(in[v], a.temperature);
+    if (w->sure || quant_detexp32(__fsub_rn(sv, w->m))) {
+      const int slot = atomicAdd(&w->count, 1);
+      if (slot < cap) list[slot] = visit_key(order_key(sv), v);
+    }
+  }
+}
+
+__global__ __launch_bounds__(kFT) void nucleus_cut_kernel(FilterArgs a, int segs) {
+  __shared__ uint64_t hist[256];
+  __shared__ uint64_t nbins[kNucBins];
+  __shared__ uint64_t cand[kCandCap];
+  __shared__ int sh_n;
+  __shared__ uint64_t red[kFW];
+  __shared__ double redd[kFW];
+  __shared__ uint32_t sh_digit;
+  __shared__ uint64_t sh_above;
+  __shared__ uint32_t s_key[2];
+  const int64_t row = blockIdx.x;
+  const int64_t V = a.V;
+  const float T = a.temperature;
+  const int tid = threadIdx.x;
+  NucleusRow* w = nucleus_row(a, row);
+  const uint64_t* list = nucleus_list(w, segs);
+  const int n = w->count;
+  const float m = w->m;
+  if (!w->live || n > nucleus_cap(segs)) {  // the list overflowed, or a row without mass
+    const float* in = a.logits + row * V;
+    float* out = a.logp + row * V;
+    const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(in) & 15) == 0 &&
+                     (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+    if (!w->live || !filter_nucleus(a, in, out, vec, nbins, cand, red, &sh_n))
+      filter_general(a, in, out, vec, hist, red, redd, &sh_digit, &sh_above);
+    if (tid == 0) a.cuts[row] = FilterCut{0, 0, 0, 1};
+    return;
+  }
+  for (int i = tid; i < n; i += kFT) cand[i] = list[i];
+  __syncthreads();
+  uint64_t cut;
+  const double lse = nucleus_kept(cand, n, m, w->before, w->tp, red, &cut);
+  const uint32_t ck = static_cast<uint32_t>(cut >> 32);
+  // logit keys whose s reaches the last kept token's, and whose s is above it
+  if (tid < 128) {
+    const uint32_t least = ck + (tid >> 6);
+    const uint32_t k = least_key([&](uint32_t q) { return order_key(__fdiv_rn(key_value(q), T)) >= least; });
+    if (lane_id() == 0) s_key[tid >> 6] = k;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    w->lse = lse;
+    a.cuts[row] = FilterCut{s_key[1], s_key[0], 0xFFFFFFFFu - static_cast<uint32_t>(cut), 0};
+  }
+}
+
+__global__ __launch_bounds__(kSegT) void nucleus_write_kernel(FilterArgs a, int segs) {
+  const int64_t row = blockIdx.x / segs, seg = blockIdx.x % segs;
+  const NucleusRow* w = nucleus_row(a, row);
+  float x[kSegU][4];
+  load_groups<kSegT, kSegU>(a.logits + row * a.V, a.V, seg * kSegElems, threadIdx.x, x);
+  const FilterCut c = a.cuts[row];
+  if (c.done) return;
+  const float m = w->m;
+  const double lse = w->lse;
+#pragma unroll
+  for (int i = 0; i < kSegU; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t k = order_key(x[i][q]);
+      const uint32_t v = static_cast<uint32_t>(seg * kSegElems + 4 * (threadIdx.x + i * kSegT) + q);
+      const bool kept = k >= c.key_above || (k >= c.key_at && v <= c.last_id);
+      float o = -INFINITY;
+      if (kept) o = log_prob(__fdiv_rn(x[i][q], a.temperature), m, lse);
+      x[i][q] = o;
+    }
+  store_groups<kSegT, kSegU>(a.logp + row * a.V, a.V, seg * kSegElems, threadIdx.x, x);
+}
+
+// One workgroup per row: every filter, for short rows and for calls without a workspace.
 __global__ __launch_bounds__(kFT) void filter_kernel(FilterArgs a) {
   __shared__ uint64_t hist[256];
   __shared__ uint64_t cand[kCandCap];
   __shared__ int resc[kFT];
   __shared__ int sh_n, sh_r;
   __shared__ uint64_t red[kFW];
+  __shared__ uint32_t redk[kFW];
   __shared__ double redd[kFW];
   __shared__ uint32_t sh_digit;
   __shared__ uint64_t sh_above;
@@ -840,185 +1628,13 @@ __global__ __launch_bounds__(kFT) void filter_kernel(FilterArgs a) {
       filter_fast(a, in, out, vec, cand, resc, red, redd, &sh_n, &sh_r))
     return;
 
-  filter_general(a, in, out, vec, hist, red, redd, &sh_digit, &sh_above);
-}
-
-// Rows with the nucleus alone (T > 0, top_k off, p < 1): the binned path, or the general one
-// when the cut's bin is too crowded.
-__global__ __launch_bounds__(kFT) void filter_nucleus_kernel(FilterArgs a) {
-  __shared__ uint64_t hist[256];
-  __shared__ uint64_t nbins[kNucBins];
-  __shared__ uint64_t cand[kCandCap];
-  __shared__ int sh_n;
-  __shared__ uint64_t red[kFW];
-  __shared__ double redd[kFW];
-  __shared__ uint32_t sh_digit;
-  __shared__ uint64_t sh_above;
-  const int64_t n = blockIdx.x;
-  const int64_t V = a.V;
-  const float* in = a.logits + n * V;
-  float* out = a.logp + n * V;
-  const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(in) & 15) == 0 &&
-                   (reinterpret_cast<uintptr_t>(out) & 15) == 0;
-  if (filter_nucleus(a, in, out, vec, nbins, cand, red, &sh_n)) return;
-  filter_general(a, in, out, vec, hist, red, redd, &sh_digit, &sh_above);
-}
-
-// Rows split over kFilterSegs workgroups (0 < k <= 256, with a workspace). A segment
-// workgroup streams its share of the row once (writing -inf, keeping each thread's four
-// largest logit keys), bounds its share's k-th largest key from below (the largest over its
-// wavefronts of each wavefront's k-th largest held key), and appends every token of its share
-// at or above that bound (in s) to the row's candidate lists in the workspace: the row's top-k
-// tokens of that share are among them, the share's k-th largest being at most the row's. A
-// merge workgroup per row then sorts the lists and writes the kept tokens. A list that
-// overflows sends the row to the general path.
-constexpr int kSegThreads = 512;
-constexpr int kSegWaves = kSegThreads / 64;
-
-__global__ __launch_bounds__(kSegThreads) void filter_seg_kernel(FilterArgs a) {
-  __shared__ int resc[kSegThreads];
-  __shared__ int sh_n, sh_r;
-  __shared__ uint32_t redk[kSegWaves];
-  const int64_t row = blockIdx.x / kFilterSegs;
-  const int seg = static_cast<int>(blockIdx.x % kFilterSegs);
-  const int tid = threadIdx.x;
-  const int64_t V = a.V;
-  const float T = a.temperature;
-  const int k = static_cast<int>(a.top_k);
-  const float* in = a.logits + row * V;
-  float* out = a.logp + row * V;
-  const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(in) & 15) == 0 &&
-                   (reinterpret_cast<uintptr_t>(out) & 15) == 0;
-  // This workgroup's units (float4 groups, or single ids): [u0, u1), thread t owns
-  // u0 + t + i * kSegThreads.
-  const int64_t units = vec ? (V >> 2) : V;
-  const int64_t per = (units + kFilterSegs - 1) / kFilterSegs;
-  const int64_t u0 = min(units, seg * per), u1 = min(units, u0 + per);
-  uint32_t t0 = 0, t1 = 0, t2 = 0, t3 = 0;
-  auto insert = [&](float lv) {
-    uint32_t x = order_key(lv);
-    uint32_t y = max(t0, x);
-    x = min(t0, x);
-    t0 = y;
-    y = max(t1, x);
-    x = min(t1, x);
-    t1 = y;
-    y = max(t2, x);
-    x = min(t2, x);
-    t2 = y;
-    t3 = max(t3, x);
-  };
-  if (vec) {
-    const float4* in4 = reinterpret_cast<const float4*>(in);
-    float4* out4 = reinterpret_cast<float4*>(out);
-    const float4 ninf = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-    int64_t j = u0 + tid;
-    for (; j + (kBatch - 1) * kSegThreads < u1; j += kBatch * kSegThreads) {
-      float4 x[kBatch];
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u) x[u] = in4[j + u * kSegThreads];
-#pragma unroll
-      for (int u = 0; u < kBatch; ++u) {
-        out4[j + u * kSegThreads] = ninf;
-        insert(x[u].x);
-        insert(x[u].y);
-        insert(x[u].z);
-        insert(x[u].w);
-      }
-    }
-    for (; j < u1; j += kSegThreads) {
-      const float4 x = in4[j];
-      out4[j] = ninf;
-      insert(x.x);
-      insert(x.y);
-      insert(x.z);
-      insert(x.w);
-    }
-  } else {
-    for (int64_t v = u0 + tid; v < u1; v += kSegThreads) {
-      insert(in[v]);
-      out[v] = -INFINITY;
-    }
-  }
-  // Lower bound of this share's k-th largest logit key.
-  const uint32_t kw = wave_kth_largest(t0, t1, t2, t3, k);
-  if (lane_id() == 0) redk[tid >> 6] = kw;
-  if (tid == 0) {
-    sh_n = 0;
-    sh_r = 0;
-  }
-  __syncthreads();
-  uint32_t tlow = 0;
-#pragma unroll
-  for (int w = 0; w < kSegWaves; ++w) tlow = max(tlow, redk[w]);
-  const uint32_t x_low = least_logit_key(order_key(__fdiv_rn(key_value(tlow), T)), T);
-  if (t0 >= x_low) resc[atomicAdd(&sh_r, 1)] = tid;
-  __syncthreads();
-  // Re-read the listed threads' units, spread over the workgroup.
-  const int nr = sh_r;
-  const int G = static_cast<int>((u1 - u0 + kSegThreads - 1) / kSegThreads);
-  const int64_t items = static_cast<int64_t>(nr) * G;
-  uint64_t* list = a.seg_cand + blockIdx.x * static_cast<int64_t>(kFilterSegCap);
-  auto take = [&](int64_t v, float lv) {
-    if (order_key(lv) >= x_low) {
-      const int slot = atomicAdd(&sh_n, 1);
-      if (slot < kFilterSegCap) list[slot] = visit_key(order_key(__fdiv_rn(lv, T)), v);
-    }
-  };
-  for (int64_t w = tid; w < items; w += kSegThreads) {
-    const int64_t j = u0 + resc[w / G] + (w % G) * static_cast<int64_t>(kSegThreads);
-    if (j >= u1) continue;
-    if (vec) {
-      const float4 x = reinterpret_cast<const float4*>(in)[j];
-      take(4 * j, x.x);
-      take(4 * j + 1, x.y);
-      take(4 * j + 2, x.z);
-      take(4 * j + 3, x.w);
-    } else {
-      take(j, in[j]);
-    }
-  }
-  __syncthreads();
-  if (tid == 0) a.seg_count[blockIdx.x] = sh_n;
-}
-
-// One workgroup per row: the row's segment lists, merged and finished; or the general path
-// when a list overflowed.
-__global__ __launch_bounds__(kFT) void filter_merge_kernel(FilterArgs a) {
-  __shared__ uint64_t hist[256];
-  __shared__ uint64_t cand[kCandCap];
-  __shared__ int sh_n;
-  __shared__ uint64_t red[kFW];
-  __shared__ double redd[kFW];
-  __shared__ uint32_t sh_digit;
-  __shared__ uint64_t sh_above;
-  const int64_t row = blockIdx.x;
-  const int64_t V = a.V;
-  const float* in = a.logits + row * V;
-  float* out = a.logp + row * V;
-  int cnt[kFilterSegs], n = 0;
-  bool over = false;
-#pragma unroll
-  for (int sgi = 0; sgi < kFilterSegs; ++sgi) {
-    cnt[sgi] = a.seg_count[row * kFilterSegs + sgi];
-    over = over || cnt[sgi] > kFilterSegCap;
-    n += cnt[sgi];
-  }
-  if (over) {
-    const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(in) & 15) == 0 &&
-                     (reinterpret_cast<uintptr_t>(out) & 15) == 0;
-    filter_general(a, in, out, vec, hist, red, redd, &sh_digit, &sh_above);
+  if ((a.top_k == 0 || a.top_k >= V) && a.top_p == 1.0f) {
+    static_assert(sizeof(cand) >= (int64_t{1} << 24) / kSegElems * sizeof(SegStat),
+                  "statistics of every segment");
+    filter_scale_row(a, in, out, reinterpret_cast<SegStat*>(cand), redk, redd);
     return;
   }
-  int base = 0;
-#pragma unroll
-  for (int sgi = 0; sgi < kFilterSegs; ++sgi) {
-    const uint64_t* list = a.seg_cand + (row * kFilterSegs + sgi) * static_cast<int64_t>(kFilterSegCap);
-    for (int i = threadIdx.x; i < cnt[sgi]; i += kFT) cand[base + i] = list[i];
-    base += cnt[sgi];
-  }
-  __syncthreads();
-  finish_candidates(a, out, cand, n, red, redd, &sh_n);
+  filter_general(a, in, out, vec, hist, red, redd, &sh_digit, &sh_above);
 }
 
 // Per sampled block: (1/b) sum_j prod_{i<=j} p(x_i); one thread per block.
@@ -1049,26 +1665,46 @@ __global__ __launch_bounds__(kFT) void determinism_mean_kernel(DeterminismArgs a
 }  // namespace
 
 hipError_t launch_filter(const FilterArgs& a, hipStream_t stream) {
-  if (a.N > 0x7fffffff / kFilterSegs) return hipErrorInvalidConfiguration;
-  const bool split = a.seg_cand && a.seg_count && a.temperature > 0.0f && a.top_k > 0 &&
-                     a.top_k <= 256 && a.top_k < a.V && a.V >= kFilterSegs * 4096;
-  const bool nucleus = a.temperature > 0.0f && (a.top_k == 0 || a.top_k >= a.V) &&
-                       a.top_p < 1.0f;
-  if (nucleus) {
-    hipLaunchKernelGGL(filter_nucleus_kernel, dim3(static_cast<unsigned>(a.N)), dim3(kFT), 0,
-                       stream, a);
-    return hipGetLastError();
+  if (a.N > 0x7fffffff) return hipErrorInvalidConfiguration;
+  const dim3 rows(static_cast<unsigned>(a.N));
+  const bool k_off = a.top_k == 0 || a.top_k >= a.V;
+  const bool nucleus = a.temperature > 0.0f && k_off && a.top_p < 1.0f;
+  const int segs = static_cast<int>(n_segs(a.V));
+  // Split rows: with a workspace, from two segments on (the whole grids below stay in range).
+  const bool split = a.row_ws && a.cuts && a.temperature > 0.0f && a.V >= kSplitMinV &&
+                     a.N <= 0x7fffffff / (segs > 16 ? segs : 16);
+  auto grid = [&](int per_row) { return dim3(static_cast<unsigned>(a.N * per_row)); };
+  hipError_t e;
+  if (a.temperature > 0.0f && k_off && !nucleus && segs <= kRowSegs) {
+    hipLaunchKernelGGL(filter_scale_rows_kernel, rows, dim3(kSegT), 0, stream, a, segs);
+  } else if (split && nucleus && a.V >= kSplitMinNucleus) {
+    const int parts = static_cast<int>((a.V + kMassElems - 1) / kMassElems);
+    hipLaunchKernelGGL(nucleus_max_kernel, grid(segs), dim3(kSegT), 0, stream, a, segs);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(nucleus_mass_kernel, grid(parts), dim3(kFT), 0, stream, a, parts, segs);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(nucleus_edge_kernel, rows, dim3(kFT), 0, stream, a, segs);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(nucleus_gather_kernel, grid(segs), dim3(kSegT), 0, stream, a, segs);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(nucleus_cut_kernel, rows, dim3(kFT), 0, stream, a, segs);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(nucleus_write_kernel, grid(segs), dim3(kSegT), 0, stream, a, segs);
+  } else if (split && k_off && !nucleus) {
+    hipLaunchKernelGGL(filter_stats_kernel, grid(segs), dim3(kSegT), 0, stream, a, segs);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(filter_scale_kernel, grid(segs), dim3(kSegT), 0, stream, a, segs);
+  } else if (split && !k_off && a.top_k <= 256) {
+    const int shares = top_shares(a.top_k);
+    hipLaunchKernelGGL(filter_topk_share_kernel, grid(shares), dim3(kTopThreads), 0, stream, a,
+                       shares);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(filter_topk_merge_kernel, rows, dim3(kFT), 0, stream, a, shares);
+  } else if (nucleus) {
+    hipLaunchKernelGGL(filter_nucleus_kernel, rows, dim3(kFT), 0, stream, a);
+  } else {
+    hipLaunchKernelGGL(filter_kernel, rows, dim3(kFT), 0, stream, a);
   }
-  if (!split) {
-    hipLaunchKernelGGL(filter_kernel, dim3(static_cast<unsigned>(a.N)), dim3(kFT), 0, stream, a);
-    return hipGetLastError();
-  }
-  hipLaunchKernelGGL(filter_seg_kernel, dim3(static_cast<unsigned>(a.N * kFilterSegs)),
-                     dim3(kSegThreads), 0, stream, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(filter_merge_kernel, dim3(static_cast<unsigned>(a.N)), dim3(kFT), 0, stream,
-                     a);
   return hipGetLastError();
 }
 

@@ -31,6 +31,27 @@ __global__ __launch_bounds__(256) void quant_all_kernel(unsigned long long* bad,
   }
 }
 
+__global__ __launch_bounds__(256) void quotient_all_kernel(float T, unsigned long long* bad,
+                                                           unsigned* first) {
+  const uint64_t u0 = (static_cast<uint64_t>(blockIdx.x) * 256 + threadIdx.x) * kPerThread;
+  const dbl::Quotient div(T);
+  unsigned long long nbad = 0;
+  unsigned fb = 0xffffffffu;
+  for (int i = 0; i < kPerThread; ++i) {
+    const uint32_t u = static_cast<uint32_t>(u0 + i);
+    const float x = __uint_as_float(u);
+    if (!(fabsf(x) <= 0x1p100f) || (fabsf(x) < 0x1p-100f && x != 0.0f)) continue;
+    if (!div.short_form || div.quick(x) != __fdiv_rn(x, T)) {
+      ++nbad;
+      fb = fb < u ? fb : u;
+    }
+  }
+  if (nbad) {
+    atomicAdd(bad, nbad);
+    atomicMin(first, fb);
+  }
+}
+
 __global__ __launch_bounds__(64) void philox01_kernel(const uint32_t* in, uint32_t* out, int n) {
   const int i = blockIdx.x * 64 + threadIdx.x;
   if (i >= n) return;
@@ -55,5 +76,14 @@ extern "C" int dbl_test_quant_exhaustive(unsigned long long* bad, unsigned* firs
   const unsigned blocks = static_cast<unsigned>((uint64_t(1) << 32) / (256 * kPerThread));
   hipLaunchKernelGGL(quant_all_kernel, dim3(blocks), dim3(256), 0,
                      static_cast<hipStream_t>(stream), bad, first);
+  return static_cast<int>(hipGetLastError());
+}
+
+// The same result words for the quotients of every dividend by T.
+extern "C" int dbl_test_quotient_exhaustive(float T, unsigned long long* bad, unsigned* first,
+                                            void* stream) {
+  const unsigned blocks = static_cast<unsigned>((uint64_t(1) << 32) / (256 * kPerThread));
+  hipLaunchKernelGGL(quotient_all_kernel, dim3(blocks), dim3(256), 0,
+                     static_cast<hipStream_t>(stream), T, bad, first);
   return static_cast<int>(hipGetLastError());
 }

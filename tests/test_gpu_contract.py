@@ -61,3 +61,24 @@ def test_kernel_philox_words_0_and_1():
         w = [int(v) for v in rows[i]]
         want = C.philox4x32_10(w[0:4], w[4:6])
         assert (int(got[i, 0]), int(got[i, 1])) == (want[0], want[1])
+
+
+@pytest.mark.gpu
+def test_short_quotient_is_correctly_rounded():
+    """The target transform's five-operation quotient against the division, for every dividend of
+    its range and temperatures across its own: ordinary ones, both ends, neighbours of powers of
+    two and significands of all ones."""
+    lib = ctypes.CDLL(HELPER)
+    f = lib.dbl_test_quotient_exhaustive
+    f.restype = ctypes.c_int
+    f.argtypes = [ctypes.c_float, ctypes.c_void_p, ctypes.c_void_p, ctypes.c_void_p]
+    dev = torch.device("cuda:0")
+    stream = torch.cuda.current_stream(dev).cuda_stream
+    one_ulp = 2.0 ** -23
+    for T in (0.6, 0.7, 0.8, 1.3, 1.5, 5.0, 1e-3, 3e4, 2.0 ** -20, 2.0 ** 20, 1 + one_ulp,
+              1 - one_ulp / 2, 2 - one_ulp, 1.75, 1 / 3):
+        bad = torch.zeros(1, dtype=torch.int64, device=dev)
+        first = torch.full((1,), -1, dtype=torch.int32, device=dev)
+        assert f(T, bad.data_ptr(), first.data_ptr(), stream) == 0
+        torch.cuda.synchronize(dev)
+        assert int(bad.item()) == 0, f"T={T}: first {int(first.item()) & 0xffffffff:#010x}"

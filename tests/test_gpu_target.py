@@ -32,6 +32,9 @@ def _logits(N, V, seed, ties=False):
         # computes the masses in every pass, not the bins alone)
         g = (-27.5 + 0.15 * synth.make_uniform_logits((N, V), seed).numpy()).astype(np.float32)
         g[:, 0] = 0.0
+    elif ties == "masked":   # the last quarter of the vocabulary is never allowed
+        g = g.astype(np.float32)
+        g[:, V - V // 4:] = -np.inf
     elif ties:   # coarse values: many equal logits at both cuts
         g = np.round(g * 2.0) / 2.0
     return g.astype(np.float32)
@@ -133,3 +136,35 @@ def test_early_determinism_parity():
     want_terms = np.exp(np.cumsum(lpx.astype(np.float64), axis=1)).mean(1)
     np.testing.assert_allclose(terms.cpu().numpy(), want_terms, rtol=1e-6, atol=1e-9)
     assert abs(mean.item() - TG.early_determinism(lpx)) < 1e-6
+
+
+# Rows split over workgroups, at the edges of their parts: two segments of 8192 ids exactly, one id
+# and one group of four more, a third segment of one id, one and two mass parts of 32,768, the share
+# counts' step at k = 128, a quarter of the vocabulary masked (whole shares without a bound), and
+# fewer ids allowed than k.
+SPLIT_EDGES = [(f"{m}-{V}{'-' + t if t else ''}", 3, V, T, k, p, t)
+               for V, t in ((16384, False), (16385, False), (16388, False), (24577, False),
+                            (32768, False), (32771, False), (40000, "masked"))
+               for m, T, k, p in (("scale", 0.7, 0, 1.0), ("nucleus", 1.3, 0, 0.9),
+                                  ("k128", 0.7, 128, 0.95), ("k129", 1.0, 129, 1.0))]
+
+
+@pytest.mark.parametrize("case", SPLIT_EDGES, ids=[c[0] for c in SPLIT_EDGES])
+def test_target_split_edges(case):
+    test_target_filter_parity(case)
+
+
+def test_target_scale_normalises():
+    """The temperature alone: every row's probabilities sum to one, in one and in many segments."""
+    from paper_2608_05448_amd import dblast as D
+    for V in (1, 5, 8192, 8193, 151936):
+        lg = torch.from_numpy(_logits(2, V, 31)).cuda()
+        for T in (0.6, 1.0, 5.0):
+            out = D.dbl_target_logprobs(lg, T)
+            assert torch.equal(out, D.dbl_target_logprobs(lg, T, split=False))
+            # s = fl32(logit / T): divided on the host, where the division is correctly rounded
+            s = torch.from_numpy(lg.cpu().numpy() / np.float32(T)).double()
+            want = torch.log_softmax(s, -1)
+            # binary32 results (half a unit of the value) of a normaliser good to 2^-32
+            err = (out.cpu().double() - want).abs()
+            assert (err <= want.abs() * 2.0 ** -23 + 2.0 ** -30).all(), (V, T, err.max())
