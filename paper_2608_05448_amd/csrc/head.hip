@@ -25,7 +25,7 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 constexpr int kVTile = 128;
 constexpr float kLog2e = 1.4426950408889634f;
@@ -175,12 +175,14 @@ __device__ __forceinline__ void tile_logsoftmax_store(f32x16 (&acc)[NRB][NCB], f
 // store instruction writes two whole 512-byte row segments. One block of 32 rows at a time:
 // its 64 logits per lane are copied out of the accumulators once; in the vocabulary's last,
 // partial tile the ids past V are set to -inf first, so every tile takes the same arithmetic.
-template <int NRB, int NCB, bool ARG>
+// MASKED: also the whole tiles of a partial 32-row block take the non-temporal stores (with few
+// branch rows that is every tile; the 256-row kernel has no registers to spare for a second form).
+template <int NRB, int NCB, bool ARG, bool MASKED = false>
 __device__ __forceinline__ void tile_logsoftmax_store_lds(f32x16 (&acc)[NRB][NCB], float* tls,
                                                           float* lmass, uint64_t* amax,
                                                           int64_t M, int64_t V, int nT,
                                                           int64_t v0w, int64_t m0w, int lane,
-                                                          int vec4, char* xp) {
+                                                          char* xp) {
   const int half = lane >> 5;
   const int lr = lane & 31;
   const int t = static_cast<int>(v0w / kVTile);
@@ -241,7 +243,6 @@ __device__ __forceinline__ void tile_logsoftmax_store_lds(f32x16 (&acc)[NRB][NCB
                   static_cast<unsigned long long>(argmax_key(mx, v0w + vi)));
     }
     float* const base = tls + (m0w + cb * 32) * V + v0w;  // wave-uniform
-    const bool fast = full && vec4 && m0w + cb * 32 + 32 <= M && V < (int64_t{1} << 25);
 #pragma unroll
     for (int rb = 0; rb < NRB; ++rb)
 #pragma unroll
@@ -263,23 +264,34 @@ __device__ __forceinline__ void tile_logsoftmax_store_lds(f32x16 (&acc)[NRB][NCB
       const int rr = 2 * jj + half;
       o[jj] = *reinterpret_cast<const float4*>(xp + rr * 512 + ((lr ^ (rr & 15)) * 16));
     }
-    if (fast) {
+    // 16-byte stores at any alignment of the row (global vector stores need 4-byte alignment only).
+    // Whole blocks are written non-temporally: the 256 KB a workgroup writes per tile would otherwise
+    // evict the operand slabs its XCD's other tiles are still reading from L2 (1% faster; where the
+    // weight is streamed once, at 64 rows and d = 2560, 168 -> 157 us).
+    const int64_t rows = M - (m0w + cb * 32);  // of this block, 32 or more if it is whole
+    if (full && rows >= 32) {
       const uint32_t lo = static_cast<uint32_t>(half * V + 4 * lr);  // 32-bit lane offsets
       const uint32_t step = static_cast<uint32_t>(2 * V);
 #pragma unroll
-      // Non-temporal: the 256 KB a workgroup writes per tile would otherwise evict the operand
-      // slabs its XCD's other tiles are still reading from L2 (1% faster).
       for (int jj = 0; jj < 16; ++jj)
-        __builtin_nontemporal_store(f32x4{o[jj].x, o[jj].y, o[jj].z, o[jj].w},
-                                    reinterpret_cast<f32x4*>(base + (lo + jj * step)));
+        __builtin_nontemporal_store(f32x4u{o[jj].x, o[jj].y, o[jj].z, o[jj].w},
+                                    reinterpret_cast<f32x4u*>(base + (lo + jj * step)));
+    } else if (MASKED && full) {
+      const uint32_t lo = static_cast<uint32_t>(half * V + 4 * lr);
+      const uint32_t step = static_cast<uint32_t>(2 * V);
+#pragma unroll
+      for (int jj = 0; jj < 16; ++jj)
+        if (2 * jj + half < rows)
+          __builtin_nontemporal_store(f32x4u{o[jj].x, o[jj].y, o[jj].z, o[jj].w},
+                                      reinterpret_cast<f32x4u*>(base + (lo + jj * step)));
     } else {
 #pragma unroll
       for (int jj = 0; jj < 16; ++jj) {
         const int rr = 2 * jj + half;
         if (m0w + cb * 32 + rr < M) {
           float* q = base + rr * V + 4 * lr;
-          if (vec4 && 4 * lr + 3 < vlim) {
-            *reinterpret_cast<float4*>(q) = o[jj];
+          if (4 * lr + 3 < vlim) {
+            *reinterpret_cast<f32x4u*>(q) = f32x4u{o[jj].x, o[jj].y, o[jj].z, o[jj].w};
           } else {
             if (4 * lr + 0 < vlim) q[0] = o[jj].x;
             if (4 * lr + 1 < vlim) q[1] = o[jj].y;
@@ -531,6 +543,20 @@ __device__ __forceinline__ int dma_swz(int r) {
 __device__ __forceinline__ void lds_dma16(const char* sbase, uint32_t voff, uint32_t m0v) {
   asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "{m0}"(m0v)
                : "memory");
+}
+
+// The same with the five wait states that a vector memory instruction needs after a VALU write of
+// its scalar base (v_readlane of a spilled base, v_readfirstlane): the compiler places them for its
+// own instructions, not in front of inline asm. For kernels with more bases than stay in scalar
+// registers.
+template <bool NT>
+__device__ __forceinline__ void lds_dma16_wait(const char* sbase, uint32_t voff, uint32_t m0v) {
+  if constexpr (NT)
+    asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1 nt" ::"v"(voff), "s"(sbase), "{m0}"(m0v)
+                 : "memory");
+  else
+    asm volatile("s_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voff), "s"(sbase), "{m0}"(m0v)
+                 : "memory");
 }
 
 // LDS byte address of a __shared__ location (the value M0 expects).
@@ -809,6 +835,13 @@ __global__ __launch_bounds__(C::kThreads, C::kWgPerCu) void head_bf16_dma_kernel
 }
 
 
+// Stages between the starting points of consecutive weight tiles: where a workgroup streams weight
+// rows whose stride is a multiple of 4 KB (d = 2048, 4096) alone, all workgroups would walk the same
+// few memory channels together if they started at the same hidden unit. Each starts its walk over d
+// kRotate stages after its neighbour and wraps around: 128 rows against a 32768 x 4096 weight
+// 69 -> 60 us, 15 rows 66 -> 50; at d = 2560 1-2%.
+constexpr int kRotate = 5;
+
 // ---------------------------------------------------------------------------------------
 // Register-staged kernel (the expander's GEMM, hidden sizes that are a multiple of 64; it was
 // the head's main path before the ping-pong kernel): 64-deep stages, so every 128-byte row
@@ -852,7 +885,7 @@ struct RsCfg {
 };
 using RsNarrow = RsCfg<128, 256, 1, 4>; // few trunk rows (the expander): 128 x 256 tiles
 
-template <class C, int EPI>
+template <class C, int EPI, bool NT>
 __global__ __launch_bounds__(C::kThreads, 1) void head_bf16_rs_kernel(
     const __bf16* __restrict__ h, const __bf16* __restrict__ w, const EpiArgs ea, int64_t M,
     int64_t V, int d, int n_mtiles) {
@@ -921,6 +954,7 @@ __global__ __launch_bounds__(C::kThreads, 1) void head_bf16_rs_kernel(
                                                             acc[rb_][cb], 0, 0, 0);
   };
   const int nk = d / BK;
+  const int k0 = kRotate * vt % nk;
   // global -> registers (stage s, clamped to the last stage) and registers -> LDS, one 16-byte
   // load of one operand at a time (q < LDA: w, else h)
   // Stages past the last (the pipeline's final three reloads) read the tile's first 16 bytes in
@@ -928,9 +962,14 @@ __global__ __launch_bounds__(C::kThreads, 1) void head_bf16_rs_kernel(
   auto gload = [&](auto buf_c, int s, int q) {
     constexpr int buf = decltype(buf_c)::value;
     const bool live = s < nk;
-    if (q < LDA)
-      ra[buf][q] = *reinterpret_cast<const u32x4*>(a_tile + (live ? a_off[q] + s * ROWB : 0u));
-    else
+    s = s + k0 < nk ? s + k0 : s + k0 - nk;
+    if (q < LDA) {
+      const u32x4* p = reinterpret_cast<const u32x4*>(a_tile + (live ? a_off[q] + s * ROWB : 0u));
+      if constexpr (NT)
+        ra[buf][q] = __builtin_nontemporal_load(p);
+      else
+        ra[buf][q] = *p;
+    } else
       rb[buf][q - LDA] =
           *reinterpret_cast<const u32x4*>(b_tile + (live ? b_off[q - LDA] + s * ROWB : 0u));
   };
@@ -1038,7 +1077,7 @@ __global__ __launch_bounds__(C::kThreads, 1) void head_bf16_rs_kernel(
     char* const xp = (jl ? (wave < 2 ? sA1 : sB1) : (wave < 2 ? sA0 : sB0)) +
                      (wave & 1) * (wave < 2 ? C::TILEA / 2 : C::TILEB / 2);
     tile_logsoftmax_store_lds<NRB, NCB, EPI == kEpiLogSoftmaxArgmax>(
-        acc, ea.tls, ea.lmass, ea.amax, M, V, ea.nT, v0w, m0 + wm * TM, lane, ea.vec4, xp);
+        acc, ea.tls, ea.lmass, ea.amax, M, V, ea.nT, v0w, m0 + wm * TM, lane, xp);
   } else
     tile_logsoftmax_store<NRB, NCB, EPI == kEpiLogSoftmaxArgmax>(
         acc, ea.tls, ea.lmass, ea.amax, M, V, ea.nT, v0w, m0 + wm * TM, lane, ea.vec4);
@@ -1220,7 +1259,173 @@ __global__ __launch_bounds__(512, 1) void head_bf16_pp_kernel(
   const int64_t v0w = v0 + wv * kVTile;
   if (v0w >= V) return;
   tile_logsoftmax_store_lds<NRB, NCB, ARG>(acc, ea.tls, ea.lmass, ea.amax, M, V, ea.nT, v0w,
-                                           m0 + wm * C::TM, lane, ea.vec4, smem + wave * 16384);
+                                           m0 + wm * C::TM, lane, smem + wave * 16384);
+}
+
+// ---------------------------------------------------------------------------------------
+// Few branch rows (the head of one or two sequences, the expander of a small batch): the weight is
+// streamed once, so HBM bounds the call, and what matters is that every CU has enough of it in
+// flight and that no CU idles. A workgroup of WV x WM x WK waves owns BV weight rows and BM branch
+// rows; each stage is KB 64-deep blocks of both, copied global -> LDS (128-byte row segments) into
+// an S-slot ring, S - 1 stages ahead, with one barrier per stage. The WK waves of a tile take every
+// WK-th 16-deep k step and their sums are added in order through LDS at the end. The weight's copies
+// are non-temporal (head, 15 rows at d = 2560: 150 -> 133 us): nothing reads it again.
+template <int BV_, int BM_, int WV_, int WM_, int WK_, int KB_, int S_>
+struct FewCfg {
+  static constexpr int BV = BV_, BM = BM_, WV = WV_, WM = WM_, WK = WK_, KB = KB_, S = S_;
+  static constexpr int NW = WV * WM * WK, kThreads = 64 * NW;
+  static constexpr int TV = BV / WV, TM = BM / WM, NRB = TV / 32, NCB = TM / 32;
+  static constexpr int ROWB = 128;                          // bytes per LDS row: 64 bf16
+  static constexpr int BLK = (BV + BM) * ROWB;              // bytes per 64-deep block
+  static constexpr int STAGE = KB * BLK;
+  static constexpr int PER = KB * (BV + BM) / 8 / NW;       // 8-row copies per wave and stage
+  static constexpr int KSTEPS = 4 * KB / WK;                // 16-deep k steps per wave and stage
+  static constexpr int kLds = S * STAGE;
+  static constexpr int kWgPerCu = 160 * 1024 / kLds;
+  static constexpr int kWavesPerEu = kWgPerCu * NW < 8 ? 1 : kWgPerCu * NW < 16 ? 2 : 4;
+  static_assert(TV % 32 == 0 && TM % 32 == 0 && 4 * KB % WK == 0, "tiling");
+  static_assert(BV / 8 % NW == 0 && BM / 8 % NW == 0, "whole row groups per wave");
+  static_assert(S >= 2 && (S - 1) * PER <= 63, "ring depth and vmcnt range");
+  static_assert(kLds <= 160 * 1024, "LDS per CU");
+  static_assert((WK - 1) * WV * WM * TV * TM * 4 <= kLds, "partial sums fit the ring");
+};
+
+template <class C, int EPI>
+__global__ __launch_bounds__(C::kThreads, C::kWavesPerEu) void head_bf16_few_kernel(
+    const __bf16* __restrict__ h, const __bf16* __restrict__ w, const EpiArgs ea, int64_t M,
+    int64_t V, int d, int n_mtiles) {
+  constexpr int NRB = C::NRB, NCB = C::NCB, ROWB = C::ROWB;
+  __shared__ __attribute__((aligned(1024))) char smem[C::kLds];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wk = wave % C::WK;
+  const int wm = wave / C::WK % C::WM;
+  const int wv = wave / C::WK / C::WM;
+  int vt, mt;
+  tile_of(xcd_remap(blockIdx.x, gridDim.x), gridDim.x / n_mtiles, n_mtiles, &vt, &mt);
+  const int64_t v0 = static_cast<int64_t>(vt) * C::BV;
+  const int64_t m0 = static_cast<int64_t>(mt) * C::BM;
+
+  // Each copy instruction covers 8 rows of a block: wave q copies the row groups q AW .. q AW + AW - 1
+  // of the weight rows and q BW .. of the branch rows; lane -> row lane / 8 of the group and the
+  // 16-byte chunk whose permuted place is lane % 8. Rows past V or M repeat the last one.
+  constexpr int AW = C::BV / 8 / C::NW, BW = C::BM / 8 / C::NW;
+  const char* const srcA = reinterpret_cast<const char*>(w + v0 * d);
+  const char* const srcB = reinterpret_cast<const char*>(h + m0 * d);
+  uint32_t offA[AW], offB[BW];
+#pragma unroll
+  for (int i = 0; i < AW; ++i) {
+    const int r = (wave * AW + i) * 8 + lane / 8;
+    const int64_t gr = r < V - v0 ? r : V - v0 - 1;
+    offA[i] = static_cast<uint32_t>(gr * d * 2 + ((lane % 8) ^ dma_swz<8>(r)) * 16);
+  }
+#pragma unroll
+  for (int i = 0; i < BW; ++i) {
+    const int r = (wave * BW + i) * 8 + lane / 8;
+    const int64_t gr = r < M - m0 ? r : M - m0 - 1;
+    offB[i] = static_cast<uint32_t>(gr * d * 2 + ((lane % 8) ^ dma_swz<8>(r)) * 16);
+  }
+  const uint32_t lds0 = lds_addr(smem);
+  const int nk = d / (64 * C::KB);
+  const int r0 = kRotate * vt % nk;
+  auto copy = [&](int s, int slot) {
+    s = s + r0 < nk ? s + r0 : s + r0 - nk;
+    const uint32_t to = lds0 + slot * C::STAGE;
+#pragma unroll
+    for (int kb = 0; kb < C::KB; ++kb) {
+      const int64_t at = (static_cast<int64_t>(s) * C::KB + kb) * 128;
+#pragma unroll
+      for (int i = 0; i < AW; ++i)
+        lds_dma16_wait<true>(srcA + at, offA[i], to + kb * C::BLK + (wave * AW + i) * 1024);
+#pragma unroll
+      for (int i = 0; i < BW; ++i)
+        lds_dma16_wait<false>(srcB + at, offB[i],
+                       to + kb * C::BLK + C::BV * ROWB + (wave * BW + i) * 1024);
+    }
+  };
+
+  f32x16 acc[NRB][NCB];
+#pragma unroll
+  for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[rb][cb][r] = 0.0f;
+
+  const int tt = 16 * ((lane >> 5) ^ dma_swz<8>(lane & 31));
+  const int a_base = (wv * C::TV + (lane & 31)) * ROWB;
+  const int b_base = (C::BV + wm * C::TM + (lane & 31)) * ROWB;
+#pragma unroll
+  for (int j = 0; j < C::S - 1; ++j)
+    if (j < nk) copy(j, j);
+  int slot = 0;
+  for (int kt = 0; kt < nk; ++kt) {
+    // Stages kt + 1 .. kt + S - 2 may still be in flight; near the end all have to be in.
+    if (kt + C::S - 1 <= nk)
+      wait_vmcnt<(C::S - 2) * C::PER>();
+    else
+      wait_vmcnt<0>();
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    // Every wave has read stage kt - 1: its slot takes stage kt + S - 1.
+    if (kt + C::S - 1 < nk) copy(kt + C::S - 1, slot == 0 ? C::S - 1 : slot - 1);
+    const char* base = smem + slot * C::STAGE;
+#pragma unroll
+    for (int j = 0; j < C::KSTEPS; ++j) {
+      const int ks = j * C::WK + wk;  // 16-deep k step of the stage
+      const char* blk = base + (ks >> 2) * C::BLK;
+      const int x = (32 * (ks & 3)) ^ tt;
+      bf16x8 af[NRB], bfr[NCB];
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb)
+        af[rb] = *reinterpret_cast<const bf16x8*>(blk + a_base + rb * 32 * ROWB + x);
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb)
+        bfr[cb] = *reinterpret_cast<const bf16x8*>(blk + b_base + cb * 32 * ROWB + x);
+#pragma unroll
+      for (int rb = 0; rb < NRB; ++rb)
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb)
+          acc[rb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[rb], bfr[cb], acc[rb][cb], 0, 0, 0);
+    }
+    slot = slot + 1 == C::S ? 0 : slot + 1;
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();  // the ring is free: nothing reads it, every copy has landed
+  asm volatile("" ::: "memory");
+
+  if constexpr (C::WK > 1) {
+    f32x16* part = reinterpret_cast<f32x16*>(smem);
+    constexpr int PT = NRB * NCB * 64;  // 16-register groups per wave tile
+    if (wk > 0) {
+#pragma unroll
+      for (int i = 0; i < NRB * NCB; ++i)
+        part[((wk - 1) * C::WV * C::WM + wv * C::WM + wm) * PT + i * 64 + lane] = acc[i / NCB][i % NCB];
+    }
+    __syncthreads();
+    if (wk == 0) {
+#pragma unroll
+      for (int p = 0; p < C::WK - 1; ++p)
+#pragma unroll
+        for (int i = 0; i < NRB * NCB; ++i)
+          acc[i / NCB][i % NCB] += part[(p * C::WV * C::WM + wv * C::WM + wm) * PT + i * 64 + lane];
+    }
+    __syncthreads();  // the epilogue stages its stores where the partial sums were
+    if (wk > 0) return;
+  }
+  const int64_t v0w = v0 + wv * C::TV;
+  if (v0w >= V) return;
+  if constexpr (EPI == kEpiExpand) {
+    expand_store<NRB, NCB>(acc, ea, M, V, v0w, m0 + wm * C::TM, lane);
+  } else {
+    static_assert(C::TV == kVTile && C::WV * C::WM * 16384 <= C::kLds,
+                  "head epilogue: 16 KB of the ring per wave that stores");
+    tile_logsoftmax_store_lds<NRB, NCB, EPI == kEpiLogSoftmaxArgmax, true>(
+        acc, ea.tls, ea.lmass, ea.amax, M, V, ea.nT, v0w, m0 + wm * C::TM, lane,
+        smem + (wv * C::WM + wm) * 16384);
+  }
 }
 
 // fp32 path: workgroup (vocabulary tile t, 4 branch rows); thread j owns id 128 t + j.
@@ -1360,6 +1565,23 @@ __global__ __launch_bounds__(256) void lse_finalize_kernel(const float* __restri
   }
 }
 
+// The head's tiles: two workgroups per CU of four waves, the 64 rows over two of them and the k steps
+// over two (up to 32 rows 135 us at d = 2560, where one wave per 32 rows took 149); above 64 rows one
+// workgroup of eight waves over 256 weight rows.
+using HeadFew64 = FewCfg<128, 64, 1, 2, 2, 1, 3>;
+using HeadFew128 = FewCfg<256, 128, 2, 4, 1, 1, 3>;
+
+template <class C, int EPI>
+hipError_t launch_few(const __bf16* h, const __bf16* w, const EpiArgs& ea, int64_t M, int64_t V,
+                      int d, hipStream_t stream) {
+  const int64_t dm = (M + C::BM - 1) / C::BM;
+  const int64_t nwg = ((V + C::BV - 1) / C::BV) * dm;
+  if (nwg > 0x7fffffff || d % (64 * C::KB) != 0) return hipErrorInvalidConfiguration;
+  hipLaunchKernelGGL((head_bf16_few_kernel<C, EPI>), dim3(static_cast<unsigned>(nwg)),
+                     dim3(C::kThreads), 0, stream, h, w, ea, M, V, d, static_cast<int>(dm));
+  return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_head(const HeadArgs& a, hipStream_t stream) {
@@ -1381,7 +1603,24 @@ hipError_t launch_head(const HeadArgs& a, hipStream_t stream) {
     const int vec4 = (a.V % 4 == 0) ? 1 : 0;
     const __bf16* h = static_cast<const __bf16*>(a.h);
     const __bf16* w = static_cast<const __bf16*>(a.w);
-    if (a.d % PpCfg::BK == 0) {
+    // Up to 128 rows the weight's stream bounds the call and a 256-row tile would be mostly padding.
+    // V = 151,936, with the LSE launch: 60 rows at d = 2560 199 -> 152 us, 128 rows 205 -> 178, 60 rows
+    // at d = 4096 299 -> 214, 120 rows 312 -> 249; from 129 rows on two 128-row tiles would stream the weight twice (180 rows at d = 2560 264 us against
+    // the ping-pong kernel's 215).
+    if (a.d % 64 == 0 && a.M <= 128) {
+      EpiArgs ea{};
+      ea.tls = a.tls;
+      ea.lmass = a.lmass;
+      ea.amax = amax;
+      ea.nT = nT;
+      const hipError_t e =
+          a.M <= HeadFew64::BM
+              ? (amax ? launch_few<HeadFew64, kEpiLogSoftmaxArgmax>(h, w, ea, a.M, a.V, a.d, stream)
+                      : launch_few<HeadFew64, kEpiLogSoftmax>(h, w, ea, a.M, a.V, a.d, stream))
+              : (amax ? launch_few<HeadFew128, kEpiLogSoftmaxArgmax>(h, w, ea, a.M, a.V, a.d, stream)
+                      : launch_few<HeadFew128, kEpiLogSoftmax>(h, w, ea, a.M, a.V, a.d, stream));
+      if (e != hipSuccess) return e;
+    } else if (a.d % PpCfg::BK == 0) {
       const int dm = static_cast<int>((a.M + PpCfg::BM - 1) / PpCfg::BM);
       const int64_t dwg = ((a.V + PpCfg::BV - 1) / PpCfg::BV) * dm;
       if (dwg > 0x7fffffff) return hipErrorInvalidConfiguration;
@@ -1515,19 +1754,55 @@ hipError_t launch_expand_rs(const ExpandArgs& a, int64_t N, hipStream_t stream) 
   ea.bias = static_cast<const __bf16*>(a.c);
   ea.hres = static_cast<const __bf16*>(a.h);
   ea.dres = a.d;
-  hipLaunchKernelGGL((head_bf16_rs_kernel<C, kEpiExpand>), dim3(static_cast<unsigned>(dwg)),
-                     dim3(C::kThreads), 0, stream, static_cast<const __bf16*>(a.h),
-                     static_cast<const __bf16*>(a.W), ea, a.M, N, a.d, dm);
+  const dim3 grid(static_cast<unsigned>(dwg)), block(C::kThreads);
+  const __bf16* h = static_cast<const __bf16*>(a.h);
+  const __bf16* w = static_cast<const __bf16*>(a.W);
+  if (dm == 1)  // the weight is read once: non-temporal (256 x 32768 x 4096: 83.5 -> 80.3 us)
+    hipLaunchKernelGGL((head_bf16_rs_kernel<C, kEpiExpand, true>), grid, block, 0, stream, h, w, ea,
+                       a.M, N, a.d, dm);
+  else
+    hipLaunchKernelGGL((head_bf16_rs_kernel<C, kEpiExpand, false>), grid, block, 0, stream, h, w, ea,
+                       a.M, N, a.d, dm);
   return hipGetLastError();
 }
+
+template <class C>
+hipError_t launch_expand_few(const ExpandArgs& a, int64_t N, hipStream_t stream) {
+  EpiArgs ea{};
+  ea.out = static_cast<__bf16*>(a.out);
+  ea.bias = static_cast<const __bf16*>(a.c);
+  ea.hres = static_cast<const __bf16*>(a.h);
+  ea.dres = a.d;
+  return launch_few<C, kEpiExpand>(static_cast<const __bf16*>(a.h),
+                                   static_cast<const __bf16*>(a.W), ea, a.M, N, a.d, stream);
+}
+
+using Few128x128 = FewCfg<128, 128, 2, 4, 1, 1, 4>;
+using Few128x64 = FewCfg<128, 64, 2, 2, 1, 1, 3>;
+using Few64x64 = FewCfg<64, 64, 2, 2, 1, 1, 4>;
+using Few64x32 = FewCfg<64, 32, 2, 1, 2, 2, 4>;
+
 hipError_t launch_expand(const ExpandArgs& a, hipStream_t stream) {
   const int64_t N = a.R * a.d;
-  const int64_t wg256 = ((N + DCfg::BV - 1) / DCfg::BV) * ((a.M + DCfg::BM - 1) / DCfg::BM);
-  if (wg256 < kCus) {
-    if (a.d % RsNarrow::BK == 0) return launch_expand_rs<RsNarrow>(a, N, stream);
-    return launch_expand_cfg<ECfg>(a, N, stream);
-  }
-  return launch_expand_cfg<DCfg>(a, N, stream);
+  auto tiles = [&](int bv, int bm) { return ((N + bv - 1) / bv) * ((a.M + bm - 1) / bm); };
+  if (tiles(DCfg::BV, DCfg::BM) >= kCus) return launch_expand_cfg<DCfg>(a, N, stream);
+  if (a.d % 64 != 0) return launch_expand_cfg<ECfg>(a, N, stream);
+  // The largest tile that still gives kFill workgroups (larger tiles read less through the L2 per
+  // weight row, smaller ones keep more CUs streaming), among those that are not mostly padding.
+  // Measured, us by tile (rows x N x d: 128 x 256, 128 x 128, 128 x 64, 64 x 64, 64 x 32):
+  //   256 x 32768 x 4096: 80, 98, 123, 156, -     256 x 16384 x 4096: 62, 49, 61, 78, -
+  //   128 x 32768 x 4096: 77, 55, 69, 89, -       128 x 16384 x 4096: 56, 45, 37, 44, -
+  //    60 x 32768 x 4096: 69, 50, 43, 51, 72      256 x 10240 x 2560: 50, 34, 46, 44, -
+  //    15 x 32768 x 4096: 64, 49, 42, 46, 46      128 x 10240 x 2560: 47, 36, 27, 32, 38
+  //   256 x  4096 x 2048: 38, 25, 20, 15, 22       60 x 10240 x 2560: 42, 30, 28, 19, 27
+  //    60 x  4096 x 2048: 33, 22, 20, 15, 12       15 x 10240 x 2560: 35, 27, 24, 17, 15
+  constexpr int64_t kFill = 160;
+  if (a.M > 128 && tiles(128, 256) >= kFill) return launch_expand_rs<RsNarrow>(a, N, stream);
+  if (a.M > 64 && tiles(128, 128) >= kFill) return launch_expand_few<Few128x128>(a, N, stream);
+  if (tiles(128, 64) >= kFill) return launch_expand_few<Few128x64>(a, N, stream);
+  if ((a.M > 32 && tiles(64, 64) >= kFill) || a.d % 128 != 0)
+    return launch_expand_few<Few64x64>(a, N, stream);
+  return launch_expand_few<Few64x32>(a, N, stream);
 }
 
 hipError_t launch_prior_head(const PriorHeadArgs& a, hipStream_t stream) {

@@ -1,14 +1,14 @@
 // Target-side sampling transform and early-determinism estimate.
 //
-// filter   one workgroup per row, or several (split rows, with a workspace): the logits divided by the temperature,
-//          restricted by top-k and then top-p, renormalised; -inf outside the kept set. Both cuts
-//          are exact selections over order-preserving 32-bit keys of s = fl32(logit / T), in
-//          general by radix (four 8-bit digit passes with LDS histograms): by count for top-k (every value equal
-//          to the k-th largest is kept), by the determinism contract's integer masses
-//          floor(detexp32(fl32(s - max)) 2^40) for top-p, where tokens are taken by decreasing s
-//          and, among equal s, increasing id, while the mass before them is below
-//          ceil(p * total). Integer histograms make the kept set independent of summation order.
-//          Temperature 0 keeps the lowest-index maximum only.
+// filter   one workgroup per row, or several (split rows, with a workspace): the logits divided by
+//          the temperature, restricted by top-k and then top-p, renormalised; -inf outside the kept
+//          set. Both cuts are exact selections over order-preserving 32-bit keys of
+//          s = fl32(logit / T), in general by radix (four 8-bit digit passes with LDS histograms):
+//          by count for top-k (every value equal to the k-th largest is kept), by the determinism
+//          contract's integer masses floor(detexp32(fl32(s - max)) 2^40) for top-p, where tokens are
+//          taken by decreasing s and, among equal s, increasing id, while the mass before them is
+//          below ceil(p * total). Integer histograms make the kept set independent of summation
+//          order. Temperature 0 keeps the lowest-index maximum only.
 // early_determinism   per sampled block, (1/b) sum_j prod_{i<=j} p(x_i); the estimate is their
 //          mean (appendix "Target-Block Early Determinism").
 #include <hip/hip_runtime.h>

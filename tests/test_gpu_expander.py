@@ -141,3 +141,19 @@ PRIOR_EDGES = [("one-load", 2, 1, 8), ("scalar", 2, 3, 77), ("below-a-round", 1,
 @pytest.mark.parametrize("case", PRIOR_EDGES, ids=[c[0] for c in PRIOR_EDGES])
 def test_prior_head_edges(case):
     test_prior_head_parity(case)
+
+
+# One shape per tile of the expander's dispatch and at its edges: 64 x 32 (32 rows and few features),
+# 64 x 64 (33 rows; any row count when d % 128 != 0), 128 x 64, 128 x 128 and 128 x 256 tiles with
+# full and ragged last row tiles.
+EXPAND_EDGES = [
+    ("64x32-one-row", 1, 1, 1, 128), ("64x32-full", 1, 32, 4, 256), ("64x64-odd-blocks", 1, 5, 3, 192),
+    ("64x64-rows", 1, 33, 40, 256), ("128x64-full", 1, 64, 40, 512), ("128x64-ragged", 1, 65, 20, 512),
+    ("128x128-ragged", 1, 100, 40, 512), ("128x128-two", 3, 43, 40, 256), ("128x256", 1, 200, 60, 384),
+    ("two-256-row-tiles", 1, 300, 30, 384),
+]
+
+
+@pytest.mark.parametrize("case", EXPAND_EDGES, ids=[c[0] for c in EXPAND_EDGES])
+def test_expander_edges(case):
+    _expander_case(*case)

@@ -135,3 +135,34 @@ def test_head_random_shapes():
         h = synth.make_uniform_logits((B, K, R, d), 300 + i).to(dt)
         w = (synth.make_uniform_logits((V, d), 400 + i) * (0.05 if bf16 else 1.0 / math.sqrt(d)))
         _check(h, w.to(dt), 2e-3 if bf16 else 2e-5, f"random-{i}")
+
+
+# Few branch rows (up to 64 and up to 128 per launch, then the 256-row tiles): row counts at the edges
+# of the 32-row blocks and of both tiles, 1 to 5 and 64 stages of 64 hidden units (fewer than the ring
+# holds, and its wrap-around), vocabularies of one id, around one and two tiles and with every
+# remainder mod 4 (unaligned rows of the output).
+@pytest.mark.parametrize("M,d,V", [
+    (1, 64, 1), (2, 64, 127), (31, 128, 129), (32, 192, 1001), (33, 256, 255), (63, 320, 1002),
+    (64, 4096, 257), (65, 64, 1003), (95, 192, 259), (97, 128, 5000), (127, 320, 130),
+    (128, 4096, 513), (129, 64, 1001),
+])
+def test_head_few_rows(M, d, V):
+    from paper_2608_05448_amd import dblast as D
+    h = synth.make_uniform_logits((1, 1, M, d) if M <= 64 else (M, 1, 1, d), 51).to(torch.bfloat16)
+    w = (synth.make_uniform_logits((V, d), 52) * (2.0 / math.sqrt(d))).to(torch.bfloat16)
+    _check(h, w, 2e-3, "few-rows")
+    # The same with the argmax, into buffers with a guard behind the last row.
+    hd, wd = h.cuda(), w.cuda()
+    lead, nT = h.shape[:-1], OH.n_tiles(V)
+    flat = [torch.full((M * n + 64,), 7.0, device="cuda") for n in (V, nT, 1)]
+    views = [f[:M * n].view(*lead, *((n,) if i < 2 else ()))
+             for i, (f, n) in enumerate(zip(flat, (V, nT, 1)))]
+    plain = D.dbl_head_logprobs(hd, wd)
+    got = D.dbl_head_logprobs(hd, wd, *views, argmax=True)
+    torch.cuda.synchronize()
+    for a, b, f in zip(plain, got, flat):
+        assert torch.equal(a, b) and bool((f[-64:] == 7.0).all())
+    lq = plain[0].view(M, V) + (plain[1] - plain[2][..., None]).view(M, nT).repeat_interleave(
+        128, dim=1)[:, :V]
+    at = lq.gather(1, got[3].view(M, 1).long())[:, 0]
+    assert bool((at >= lq.max(1).values - 1e-5).all())
