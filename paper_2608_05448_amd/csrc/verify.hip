@@ -16,7 +16,7 @@
 //   finalize  one 256-thread workgroup per block: acceptance masses,
 //             E = sum_i prod_{j<=i} beta_j, and the residual/bonus inverse-CDF draw (the tile
 //             from the tile sums, then the tile's weights staged in LDS in one round of loads).
-//   stream    (verification with V % 4 == 0 and masses requested: the usual case) beta and
+//   stream    (verification with masses requested and V >= 4: the usual case) beta and
 //             residual in one launch between the chain and finalize: the residual's tile sums
 //             come from the stream's own loads at the first rejected position.
 // The expected-length reduction along a given trajectory runs chain, beta and finalize (no
@@ -273,16 +273,17 @@ __device__ __forceinline__ void beta_body(const VerifyArgs& a, int64_t pos, int 
   const float* prow = a.logp + (b * a.Kp + k) * V;
   const float* trow = k_.tls + m0 * V;
   float acc = 0.0f;
-  if ((V & 3) == 0) {
+  if (V >= 4) {
     for (int64_t v = vb + 4 * threadIdx.x; v < ve; v += 4 * blockDim.x) {
       const int tt = static_cast<int>((v - vb) >> 7);
-      const float4 p = load_stream4(prow + v);
+      const RowGroup g(v, V);
+      const float4 p = g.target(prow);
       float4 x[RT > 0 ? RT : 1];
       float q0 = 0.0f, q1 = 0.0f, q2 = 0.0f, q3 = 0.0f;
       if constexpr (RT > 0) {
-#pragma unroll
-        for (int z = 0; z < RT; ++z) x[z] = load_stream4(trow + z * V + v);
-#pragma unroll
+  #pragma unroll
+        for (int z = 0; z < RT; ++z) x[z] = g.branch(trow + z * V);
+  #pragma unroll
         for (int z = 0; z < RT; ++z) {
           const float o = s_off[z][tt], w = s_w[z];
           q0 = fmaf(w, __builtin_amdgcn_exp2f(fmaf(x[z].x, kLog2eF, o)), q0);
@@ -292,7 +293,7 @@ __device__ __forceinline__ void beta_body(const VerifyArgs& a, int64_t pos, int 
         }
       } else {
         for (int z = 0; z < R; ++z) {
-          const float4 xz = load_stream4(trow + z * V + v);
+          const float4 xz = g.branch(trow + z * V);
           const float o = s_off[z][tt], w = s_w[z];
           q0 = fmaf(w, __builtin_amdgcn_exp2f(fmaf(xz.x, kLog2eF, o)), q0);
           q1 = fmaf(w, __builtin_amdgcn_exp2f(fmaf(xz.y, kLog2eF, o)), q1);
@@ -307,10 +308,9 @@ __device__ __forceinline__ void beta_body(const VerifyArgs& a, int64_t pos, int 
     }
   } else {
     for (int64_t v = vb + threadIdx.x; v < ve; v += blockDim.x) {
-      const int tt = static_cast<int>((v - vb) >> 7);
       float q = 0.0f;
       for (int z = 0; z < R; ++z)
-        q = fmaf(s_w[z], __builtin_amdgcn_exp2f(fmaf(trow[z * V + v], kLog2eF, s_off[z][tt])), q);
+        q = fmaf(s_w[z], __builtin_amdgcn_exp2f(fmaf(trow[z * V + v], kLog2eF, s_off[z][0])), q);
       acc += fminf(__builtin_amdgcn_exp2f(prow[v] * kLog2eF), q);
     }
   }
@@ -455,18 +455,6 @@ __global__ __launch_bounds__(256) void residual_kernel(VerifyArgs a) {
   residual_body<RT>(a, blockIdx.x, blockIdx.y);
 }
 
-// Residual / bonus tile sums and the acceptance-mass stream in one launch: workgroups
-// x < B are the residual's (issued first, so its ALU-heavy blocks overlap the stream), the rest
-// the acceptance-mass stream's. The two write disjoint outputs.
-template <int RT>
-__global__ __launch_bounds__(256) void beta_residual_kernel(VerifyArgs a) {
-  const int64_t B = a.blk.B;
-  if (blockIdx.x < B)
-    residual_body<RT>(a, blockIdx.x, blockIdx.y);
-  else
-    beta_body<RT>(a, blockIdx.x - B, blockIdx.y, gridDim.y);
-}
-
 // Block b: acceptance masses and E (binary64 sums of the chunk partials), then the residual or
 // bonus draw by inverse CDF over the tile sums. Run by a whole 256-thread workgroup.
 constexpr int kStageBatch = 8;  // loads in flight per thread when staging a tile's branch values
@@ -608,8 +596,8 @@ __global__ __launch_bounds__(256) void finalize_kernel(VerifyArgs a, int nchunk)
   finalize_block(a, blockIdx.x, nchunk);
 }
 
-// The acceptance-mass stream with the residual tile sums folded in (V % 4 == 0, masses
-// requested). Workgroup g handles chunk c = g % nchunk (stream_tiles(R) vocabulary tiles: 40, or
+// The acceptance-mass stream with the residual tile sums folded in (masses requested, V >= 4: rows
+// are read in groups of four ids at any alignment). Workgroup g handles chunk c = g % nchunk (stream_tiles(R) vocabulary tiles: 40, or
 // 32 at R <= 4, where cpw consecutive chunks share a workgroup) of position row k of block b,
 // g / nchunk = k B + b:
 //  * k < K: the R branch rows and the target row of the chunk are read once for the
@@ -703,13 +691,14 @@ void verify_stream_kernel(VerifyArgs a, int nchunk, int cpw) {
       const int tt = (4 * tid + 1024 * i) >> 7;  // the 32 threads of a half-wave share a tile
       uint64_t sp = 0, sr = 0;
       if (v < ve) {
-        const float4 p = load_stream4(prow + v);
+        const RowGroup g(v, V);
+        const float4 p = g.target(prow);
         if (!bonus && !res) {
           float q0 = 0.0f, q1 = 0.0f, q2 = 0.0f, q3 = 0.0f;
           if constexpr (RT > 0) {
             float4 x[RT];
 #pragma unroll
-            for (int z = 0; z < RT; ++z) x[z] = load_stream4(trow + z * V + v);
+            for (int z = 0; z < RT; ++z) x[z] = g.branch(trow + z * V);
 #pragma unroll
             for (int z = 0; z < RT; ++z) {
               const float o = s_offx[z][tt] * kLog2eChunk, w = s_w[z];
@@ -720,7 +709,7 @@ void verify_stream_kernel(VerifyArgs a, int nchunk, int cpw) {
             }
           } else {
             for (int z = 0; z < R; ++z) {
-              const float4 xz = load_stream4(trow + z * V + v);
+              const float4 xz = g.branch(trow + z * V);
               const float o = s_offx[z][tt] * kLog2eChunk, w = s_w[z];
               q0 = fmaf(w, __builtin_amdgcn_exp2f(fmaf(xz.x, kLog2eChunk, o)), q0);
               q1 = fmaf(w, __builtin_amdgcn_exp2f(fmaf(xz.y, kLog2eChunk, o)), q1);
@@ -742,7 +731,7 @@ void verify_stream_kernel(VerifyArgs a, int nchunk, int cpw) {
           double Q[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll 1
           for (int z = 0; z < R; ++z) {
-            const float4 xz = load_stream4(trow + z * V + v);
+            const float4 xz = g.branch(trow + z * V);
             const float xe[4] = {xz.x, xz.y, xz.z, xz.w};
             const float oz = s_offx[z][tt];
             const float o = oz * kLog2eChunk, w = s_w[z];
@@ -792,7 +781,139 @@ void verify_stream_kernel(VerifyArgs a, int nchunk, int cpw) {
   }
 }
 
+// The same work where the whole grid fits the chip at once (one or a few sequences, short
+// vocabularies): latency bounds it, so 1024 threads take a chunk of 32 tiles in one step. The chunk's
+// loads are issued before anything else (the tile offsets and weights arrive meanwhile), and at the
+// first rejected position every branch row is in flight at once, where the kernel above walks the
+// categories with one load each: that walk, four steps long, was most of its time (one sequence, K = 15,
+// R = 4: 22 -> 13 us; K = 16, R = 8 the call 55 -> 31).
+template <int RT>
+__global__ __launch_bounds__(1024) void verify_stream_wide_kernel(VerifyArgs a, int nchunk) {
+  constexpr int TPC = kTilesPerChunk;
+  constexpr int ZB = RT > 0 ? RT : 8;  // categories whose loads are in flight together
+  static_assert(TPC * kTile == 4 * 1024, "four ids per thread");
+  const BlockArgs& k_ = a.blk;
+  const int64_t B = k_.B;
+  const int c = static_cast<int>(blockIdx.x % static_cast<unsigned>(nchunk));
+  const int64_t pb = blockIdx.x / static_cast<unsigned>(nchunk);
+  const int64_t k = pb / B, b = pb % B;
+  const int R = RT > 0 ? RT : static_cast<int>(k_.R);
+  const int64_t V = k_.V;
+  const int tid = threadIdx.x;
+  __shared__ float s_w[kMaxR];
+  __shared__ double s_wz[kMaxR];
+  __shared__ float s_offx[kMaxR][TPC];  // fl32(lmass - lse) of the chunk's tiles
+  __shared__ float red[16];
+  const bool bonus = k == k_.K;
+  const int64_t m0 = (b * k_.K + k) * k_.R;  // first branch row of the position (k < K)
+  const int t0 = c * TPC;
+  const int nt = min(TPC, k_.nT - t0);
+  const int tt = tid >> 5;  // the 32 threads of a half-wave share a tile
+  // Threads past the row repeat its last group with every target value masked.
+  const RowGroup g(static_cast<int64_t>(t0) * kTile + 4 * tid, V);
+  const float* prow = a.logp + (b * a.Kp + k) * V;
+  const float* trow = k_.tls + m0 * V;
+  float4 p = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+  float4 x[ZB];
+  auto load_rows = [&](int z0) {
+#pragma unroll
+    for (int z = 0; z < ZB; ++z) x[z] = g.branch(trow + min(z0 + z, R - 1) * V);
+  };
+  if (!bonus) {
+    p = g.target(prow);
+    load_rows(0);
+    for (int i = tid; i < R * TPC; i += 1024) {
+      const int z = i / TPC, t = i % TPC;
+      if (t < nt) s_offx[z][t] = k_.lmass[(m0 + z) * k_.nT + t0 + t] - k_.lse[m0 + z];
+    }
+    if (tid < R) {
+      const double wv = a.wpost[m0 + tid];
+      s_w[tid] = static_cast<float>(wv);
+      s_wz[tid] = wv;
+    }
+  }
+  const int ks = a.n_accept[b];  // first rejected position, K if none
+  __syncthreads();
+  const bool res = bonus ? ks == k_.K : k == ks;
+  if (bonus && !res) return;  // workgroup-uniform
+  uint64_t sp = 0, sr = 0;
+  if (bonus) p = g.target(prow);
+  const float pe[4] = {p.x, p.y, p.z, p.w};
+  if (!bonus) {
+    float q[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    double Q[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int z0 = 0; z0 < R; z0 += ZB) {
+      if (z0 > 0) load_rows(z0);
+#pragma unroll
+      for (int z = 0; z < ZB; ++z) {
+        if (RT == 0 && z0 + z >= R) break;
+        const float xe[4] = {x[z].x, x[z].y, x[z].z, x[z].w};
+        const float o = s_offx[z0 + z][tt] * kLog2eChunk, w = s_w[z0 + z];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          q[e] = fmaf(w, __builtin_amdgcn_exp2f(fmaf(xe[e], kLog2eChunk, o)), q[e]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (res) {
+#pragma unroll
+        for (int z = 0; z < ZB; ++z) {
+          if (RT == 0 && z0 + z >= R) break;
+          const float xe[4] = {x[z].x, x[z].y, x[z].z, x[z].w};
+          const float oz = s_offx[z0 + z][tt];
+          const double wz = s_wz[z0 + z];
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            Q[e] = __dadd_rn(Q[e], __dmul_rn(wz, static_cast<double>(detexp32(__fadd_rn(xe[e], oz)))));
+          __builtin_amdgcn_sched_barrier(0);  // one category's temporaries at a time
+        }
+      }
+    }
+    float acc = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc += fminf(__builtin_amdgcn_exp2f(pe[e] * kLog2eChunk), q[e]);
+    if (tt >= nt) acc = 0.0f;  // past the row's tiles the offsets are not set
+    acc = wave_sum_f32(acc);
+    if ((tid & 63) == 0) red[tid >> 6] = acc;
+    if (res)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const uint64_t P = quant_detexp32(pe[e]);
+        const uint64_t Qi = quant40d(Q[e]);
+        sr += P > Qi ? P - Qi : 0;
+        sp += P;
+      }
+    __syncthreads();
+    if (tid < 64) {
+      float s = tid < 16 ? red[tid] : 0.0f;
+#pragma unroll
+      for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o);
+      if (tid == 0) a.beta_part[(b * k_.K + k) * nchunk + c] = s;
+    }
+  } else {  // the bonus row after full acceptance: P only
+#pragma unroll
+    for (int e = 0; e < 4; ++e) sp += quant_detexp32(pe[e]);
+  }
+  if (res) {
+#pragma unroll
+    for (int o = 16; o > 0; o >>= 1) {
+      sp += __shfl_xor(sp, o);
+      sr += __shfl_xor(sr, o);
+    }
+    if ((tid & 31) == 0 && tt < nt) {
+      a.p_tiles[b * k_.nT + t0 + tt] = sp;
+      if (!bonus) a.res_tiles[b * k_.nT + t0 + tt] = sr;
+    }
+  }
+}
+
 }  // namespace
+
+// Grids up to this many 1024-thread workgroups take the wide stream kernel. Whole calls with the bonus
+// row, 256 threads against 1024: 608 workgroups (K = 15, R = 4) 33 and 27 us, 1216 (two sequences) 37
+// and 33, 1254 (three sequences, K = 10, R = 8) 62 and 46, 1824 43 and 44, 2432 (R = 2) 33 and 35, 3040
+// 51 and 61. A row of up to eight tiles is one step of 256 threads already.
+constexpr int64_t kWideMaxGroups = 1280;
+constexpr int kWideMinTiles = 8;
 
 hipError_t launch_verify(const VerifyArgs& a, hipStream_t stream) {
   const int64_t B = a.blk.B;
@@ -807,16 +928,33 @@ hipError_t launch_verify(const VerifyArgs& a, hipStream_t stream) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const bool want_beta = a.beta || a.exp_len;
-  const bool stream_path = want_beta && (a.blk.V & 3) == 0 && !a.trajectory;
+  const bool stream_path = want_beta && !a.trajectory && a.blk.V >= 4;  // a row holds a group of four
   int nchunk_f = nchunk;  // the finalisation's partials per position
-  if (stream_path) {
+  const int rows = static_cast<int>(a.blk.K) + (!a.trajectory && a.Kp == a.blk.K + 1 ? 1 : 0);
+  if (stream_path && a.blk.nT > kWideMinTiles && rows * B * nchunk <= kWideMaxGroups) {
+    const dim3 grid(static_cast<unsigned>(rows * B * nchunk));
+#define DBL_WIDE(r) \
+  case r: hipLaunchKernelGGL(verify_stream_wide_kernel<r>, grid, dim3(1024), 0, stream, a, nchunk); break
+    switch (a.blk.R) {
+      DBL_WIDE(1);
+      DBL_WIDE(2);
+      DBL_WIDE(3);
+      DBL_WIDE(4);
+      DBL_WIDE(5);
+      DBL_WIDE(6);
+      DBL_WIDE(7);
+      DBL_WIDE(8);
+      default: hipLaunchKernelGGL(verify_stream_wide_kernel<0>, grid, dim3(1024), 0, stream, a, nchunk);
+    }
+#undef DBL_WIDE
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  } else if (stream_path) {
     // One stream: acceptance masses, and the residual tile sums at the first rejection from the
     // same loads. Trajectory mode keeps the beta kernel below: its stream has no residual
     // arithmetic to carry, and at R = 16 it measured 3.48 ms against 3.78 ms fused per 128-block
     // chunk.
-    const int rows = static_cast<int>(a.blk.K) + (!a.trajectory && a.Kp == a.blk.K + 1 ? 1 : 0);
     const int64_t R = a.blk.R;  // the template argument of the launch below: R, or 0
-    const int rt = R == 1 || R == 2 || R == 4 || R == 8 || R == 16 ? static_cast<int>(R) : 0;
+    const int rt = R <= 8 || R == 16 ? static_cast<int>(R) : 0;
     const int nchunk_s = (a.blk.nT + stream_tiles(rt) - 1) / stream_tiles(rt);
     nchunk_f = nchunk_s;
     const int64_t cw_many = (nchunk_s + kStreamChunksSmallR - 1) / kStreamChunksSmallR;
@@ -828,22 +966,14 @@ hipError_t launch_verify(const VerifyArgs& a, hipStream_t stream) {
     switch (a.blk.R) {
       case 1: hipLaunchKernelGGL(verify_stream_kernel<1>, grid, dim3(256), 0, stream, a, nchunk_s, cpw); break;
       case 2: hipLaunchKernelGGL(verify_stream_kernel<2>, grid, dim3(256), 0, stream, a, nchunk_s, cpw); break;
+      case 3: hipLaunchKernelGGL(verify_stream_kernel<3>, grid, dim3(256), 0, stream, a, nchunk_s, cpw); break;
       case 4: hipLaunchKernelGGL(verify_stream_kernel<4>, grid, dim3(256), 0, stream, a, nchunk_s, cpw); break;
+      case 5: hipLaunchKernelGGL(verify_stream_kernel<5>, grid, dim3(256), 0, stream, a, nchunk_s, cpw); break;
+      case 6: hipLaunchKernelGGL(verify_stream_kernel<6>, grid, dim3(256), 0, stream, a, nchunk_s, cpw); break;
+      case 7: hipLaunchKernelGGL(verify_stream_kernel<7>, grid, dim3(256), 0, stream, a, nchunk_s, cpw); break;
       case 8: hipLaunchKernelGGL(verify_stream_kernel<8>, grid, dim3(256), 0, stream, a, nchunk_s, cpw); break;
       case 16: hipLaunchKernelGGL(verify_stream_kernel<16>, grid, dim3(256), 0, stream, a, nchunk_s, cpw); break;
       default: hipLaunchKernelGGL(verify_stream_kernel<0>, grid, dim3(256), 0, stream, a, nchunk_s, cpw); break;
-    }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  } else if (want_beta && !a.trajectory) {
-    if (npos + B > 0x7fffffff) return hipErrorInvalidConfiguration;
-    const dim3 grid(static_cast<unsigned>(B + npos), nchunk);
-    switch (a.blk.R) {
-      case 1: hipLaunchKernelGGL(beta_residual_kernel<1>, grid, dim3(256), 0, stream, a); break;
-      case 2: hipLaunchKernelGGL(beta_residual_kernel<2>, grid, dim3(256), 0, stream, a); break;
-      case 4: hipLaunchKernelGGL(beta_residual_kernel<4>, grid, dim3(256), 0, stream, a); break;
-      case 8: hipLaunchKernelGGL(beta_residual_kernel<8>, grid, dim3(256), 0, stream, a); break;
-      case 16: hipLaunchKernelGGL(beta_residual_kernel<16>, grid, dim3(256), 0, stream, a); break;
-      default: hipLaunchKernelGGL(beta_residual_kernel<0>, grid, dim3(256), 0, stream, a); break;
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
   } else if (want_beta) {
@@ -857,7 +987,8 @@ hipError_t launch_verify(const VerifyArgs& a, hipStream_t stream) {
       default: hipLaunchKernelGGL(beta_kernel<0>, grid, dim3(256), 0, stream, a); break;
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
-  } else if (!a.trajectory) {
+  }
+  if (!a.trajectory && !stream_path) {
     const dim3 grid(static_cast<unsigned>(B), nchunk);
     switch (a.blk.R) {
       case 1: hipLaunchKernelGGL(residual_kernel<1>, grid, dim3(256), 0, stream, a); break;

@@ -28,6 +28,32 @@ __device__ __forceinline__ float4 load_stream4(const float* p) {
 #endif
 }
 
+// The same at any 4-byte aligned address (all that a vector load from global memory needs), for rows
+// whose length 4 does not divide.
+typedef float stream_f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 load_stream4u(const float* p) {
+  const stream_f32x4u v = __builtin_nontemporal_load(reinterpret_cast<const stream_f32x4u*>(p));
+  return make_float4(v.x, v.y, v.z, v.w);
+}
+// The four ids v .. v + 3 of a row of V >= 4: where the row ends among them they are read from
+// at = V - 4 on, and the first v - at of the target's values, which the ids before v hold, are set to
+// -inf (p = 0: nothing is added for them, whatever the branch values). No load has a condition.
+struct RowGroup {
+  uint32_t at;  // 32 bits (V < 2^24): one register of lane offset on a scalar row address
+  int drop;
+  __device__ RowGroup(int64_t v, int64_t V)
+      : at(static_cast<uint32_t>(v < V - 4 ? v : V - 4)), drop(static_cast<int>(v - at)) {}
+  __device__ float4 target(const float* row) const {
+    float4 p = load_stream4u(row + at);
+    p.x = drop > 0 ? -INFINITY : p.x;
+    p.y = drop > 1 ? -INFINITY : p.y;
+    p.z = drop > 2 ? -INFINITY : p.z;
+    p.w = drop > 3 ? -INFINITY : p.w;  // all of a group past the row's end
+    return p;
+  }
+  __device__ float4 branch(const float* row) const { return load_stream4u(row + at); }
+};
+
 // Value of lane l (wave-uniform l) in every lane: v_readlane on each 32-bit half, a few cycles
 // instead of an LDS-crossbar shuffle.
 __device__ __forceinline__ uint64_t lane_u64(uint64_t v, int l) {

@@ -246,3 +246,24 @@ def test_random_shapes_against_the_oracle():
         beta_o, e_o = MX.expected_len_blocks(c.lq, c.ell, zt, xs, c.logp[:, :K])
         _rel_close(beta_g.cpu().numpy(), beta_o)
         _rel_close(e_g.cpu().numpy(), e_o)
+
+
+# The verification streams at the edges of their ranges: rows of one group of four ids and one past it
+# (below four the separate kernels run), eight tiles and nine (from where a small grid takes 1024
+# threads per chunk), one chunk of 32 tiles and one id or one group into the next, every remainder mod
+# 4, category counts with a kernel of their own and 9, 11 and 16 (batches of eight), and grids past the
+# wide kernel's limit with unaligned rows.
+STREAM_EDGES = [
+    (f"edge-{V}-r{R}", B, K, R, V, 8, "aligned-block", kx, 1.0, 1.0, V, 0, 0)
+    for B, K, R, V, kx in ((5, 3, 2, 3, 1), (5, 3, 3, 4, 1), (5, 3, 5, 5, 0), (6, 4, 3, 1024, 1),
+                           (6, 4, 5, 1025, 1), (6, 4, 6, 1026, 0), (6, 4, 7, 1155, 1),
+                           (4, 3, 9, 4096, 1), (4, 3, 1, 4097, 1), (4, 3, 8, 4098, 0),
+                           (4, 3, 16, 4101, 1), (3, 3, 11, 4227, 1), (3, 2, 4, 8193, 1),
+                           (190, 6, 6, 1102, 1), (190, 6, 3, 1103, 1), (190, 6, 7, 1101, 1),
+                           (190, 6, 5, 1100, 1))
+]
+
+
+@pytest.mark.parametrize("case", STREAM_EDGES, ids=[c[0] for c in STREAM_EDGES])
+def test_stream_edges(case):
+    test_sample_verify_parity(case)
