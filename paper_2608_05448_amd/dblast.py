@@ -8,6 +8,7 @@ kernels. There is no fallback: if the library is not built or no GPU is visible,
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 import torch
@@ -94,15 +95,27 @@ def _check(status: int):
                           lib.dbl_status_string(status).decode())
 
 
+# Small calls are bound by this module's own time (verification of one sequence took 27 us of host
+# time for 25 us on the GPU, a tiny step 61), so the checks of a valid tensor are one expression, sizes
+# are looked up rather than computed twice, outputs come from new_empty and addresses go to ctypes as
+# plain integers.
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    if _raw_stream is not None and device.index is not None:
+        return _raw_stream(device.index)
+    return torch.cuda.current_stream(device).cuda_stream
 
 
 def _need(t, name, dtype, shape=None):
+    if (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous()
+            and (shape is None or t.shape == shape)):
+        return
     if not isinstance(t, torch.Tensor):
         raise TypeError(f"{name} must be a torch.Tensor")
     if t.device.type != "cuda":
@@ -119,12 +132,13 @@ def ntiles(V: int) -> int:
     return (V + VTILE - 1) // VTILE
 
 
+@functools.lru_cache(maxsize=1024)
 def dbl_workspace_bytes(op: int, B: int, K: int, R: int, d: int, V: int) -> int:
     return int(load().dbl_workspace_bytes(op, Shape(B, K, R, d, V)))
 
 
 def _workspace(op, shape, device, ws=None):
-    n = int(load().dbl_workspace_bytes(op, shape))
+    n = dbl_workspace_bytes(op, shape.B, shape.K, shape.R, shape.d, shape.V)
     if n == 0:
         return None, 0
     if ws is not None:
@@ -150,9 +164,9 @@ def dbl_head_logprobs(h, w, tls=None, lmass=None, lse=None, argmax=None, ws=None
     dev = h.device
     nT = ntiles(V)
     tls = torch.empty((B, K, R, V), dtype=torch.float32, device=dev) if tls is None else tls
-    lmass = torch.empty((B, K, R, nT), dtype=torch.float32, device=dev) if lmass is None else lmass
-    lse = torch.empty((B, K, R), dtype=torch.float32, device=dev) if lse is None else lse
     _need(tls, "tls", torch.float32, (B, K, R, V))
+    lmass = tls.new_empty((B, K, R, nT)) if lmass is None else lmass
+    lse = tls.new_empty((B, K, R)) if lse is None else lse
     _need(lmass, "lmass", torch.float32, (B, K, R, nT))
     _need(lse, "lse", torch.float32, (B, K, R))
     shape = Shape(B, K, R, d, V)
@@ -184,15 +198,32 @@ def dbl_sample_block(tls, lmass, lse, prior_logits, z_temp=1.0, seed=0, step=0, 
     """Draw one block per sequence: returns (z [B] int32, x [B, K] int32)."""
     shape = _block_shape(tls, lmass, lse, prior_logits)
     dev = tls.device
-    z_out = torch.empty(shape.B, dtype=torch.int32, device=dev) if z_out is None else z_out
-    x_out = torch.empty((shape.B, shape.K), dtype=torch.int32, device=dev) if x_out is None else x_out
-    _need(z_out, "z_out", torch.int32, (shape.B,))
-    _need(x_out, "x_out", torch.int32, (shape.B, shape.K))
+    B, K = shape.B, shape.K
+    z_out = torch.empty(B, dtype=torch.int32, device=dev) if z_out is None else z_out
+    _need(z_out, "z_out", torch.int32, (B,))
+    x_out = z_out.new_empty((B, K)) if x_out is None else x_out
+    _need(x_out, "x_out", torch.int32, (B, K))
     ws, nws = _workspace(DBL_OP_SAMPLE, shape, dev, ws)
     _check(load().dbl_sample_block(shape, _ptr(tls), _ptr(lmass), _ptr(lse), _ptr(prior_logits),
                                    float(z_temp), int(seed), int(step), int(seq_offset),
                                    _ptr(z_out), _ptr(x_out), _ptr(ws), nws, _stream(dev)))
     return z_out, x_out
+
+
+def _verify_outputs(out, like, B, K, want_beta, want_al, want_exp_len):
+    """The caller's outputs with the missing ones added, on the device of ``like``."""
+    o = {} if out is None else dict(out)
+    if "n_accept" not in o:
+        o["n_accept"] = like.new_empty(B, dtype=torch.int32)
+    if "next_token" not in o:
+        o["next_token"] = like.new_empty(B, dtype=torch.int32)
+    if want_beta and "accept_mass" not in o:
+        o["accept_mass"] = like.new_empty((B, K), dtype=torch.float32)
+    if want_al and "al_expected" not in o:
+        o["al_expected"] = like.new_empty(B, dtype=torch.float32)
+    if want_exp_len and "exp_len" not in o:
+        o["exp_len"] = like.new_empty(B, dtype=torch.float32)
+    return o
 
 
 def dbl_verify_block(tls, lmass, lse, prior_logits, x, logp, z_temp=1.0, seed=0, step=0,
@@ -211,15 +242,7 @@ def dbl_verify_block(tls, lmass, lse, prior_logits, x, logp, z_temp=1.0, seed=0,
         raise ValueError("logp must be [B, Kp, V]")
     _need(logp, "logp", torch.float32)
     Kp = logp.shape[1]
-    o = {} if out is None else dict(out)
-    o.setdefault("n_accept", torch.empty(B, dtype=torch.int32, device=dev))
-    o.setdefault("next_token", torch.empty(B, dtype=torch.int32, device=dev))
-    if want_beta:
-        o.setdefault("accept_mass", torch.empty((B, K), dtype=torch.float32, device=dev))
-    if want_al:
-        o.setdefault("al_expected", torch.empty(B, dtype=torch.float32, device=dev))
-    if want_exp_len:
-        o.setdefault("exp_len", torch.empty(B, dtype=torch.float32, device=dev))
+    o = _verify_outputs(out, tls, B, K, want_beta, want_al, want_exp_len)
     ws, nws = _workspace(DBL_OP_VERIFY, shape, dev, ws)
     _check(load().dbl_verify_block(shape, _ptr(tls), _ptr(lmass), _ptr(lse), _ptr(prior_logits),
                                    float(z_temp), _ptr(x), _ptr(logp), int(Kp), int(seed),
@@ -243,15 +266,7 @@ def dbl_verify_block_static(tls, lmass, lse, prior_logits, x, logp, z_temp=1.0, 
         raise ValueError("logp must be [B, Kp, V]")
     _need(logp, "logp", torch.float32)
     Kp = logp.shape[1]
-    o = {} if out is None else dict(out)
-    o.setdefault("n_accept", torch.empty(B, dtype=torch.int32, device=dev))
-    o.setdefault("next_token", torch.empty(B, dtype=torch.int32, device=dev))
-    if want_beta:
-        o.setdefault("accept_mass", torch.empty((B, K), dtype=torch.float32, device=dev))
-    if want_al:
-        o.setdefault("al_expected", torch.empty(B, dtype=torch.float32, device=dev))
-    if want_exp_len:
-        o.setdefault("exp_len", torch.empty(B, dtype=torch.float32, device=dev))
+    o = _verify_outputs(out, tls, B, K, want_beta, want_al, want_exp_len)
     _check(load().dbl_verify_block_static(shape, _ptr(tls), _ptr(lmass), _ptr(lse),
                                           _ptr(prior_logits), float(z_temp), _ptr(x), _ptr(logp),
                                           int(Kp), int(seed), int(step), int(seq_offset),
@@ -270,8 +285,8 @@ def dbl_expected_len(tls, lmass, lse, prior_logits, x, logp, z_temp=1.0, want_be
     _need(x, "x", torch.int32, (B, K))
     _need(logp, "logp", torch.float32, (B, K, V))
     if want_beta and beta is None:
-        beta = torch.empty((B, K), dtype=torch.float32, device=dev)
-    exp_len = torch.empty(B, dtype=torch.float32, device=dev) if exp_len is None else exp_len
+        beta = tls.new_empty((B, K))
+    exp_len = tls.new_empty(B) if exp_len is None else exp_len
     ws, nws = _workspace(DBL_OP_EXPECTED_LEN, shape, dev, ws)
     _check(load().dbl_expected_len(shape, _ptr(tls), _ptr(lmass), _ptr(lse), _ptr(prior_logits),
                                    float(z_temp), _ptr(x), _ptr(logp), _ptr(beta), _ptr(exp_len),
@@ -292,10 +307,11 @@ def dbl_sample_greedy(x_hat, prior_logits, z_temp=1.0, seed=0, step=0, seq_offse
     ``V`` is only used for shape validation (the draw reads no vocabulary row)."""
     shape = _greedy_shape(x_hat, prior_logits, V)
     dev = x_hat.device
-    z_out = torch.empty(shape.B, dtype=torch.int32, device=dev) if z_out is None else z_out
-    x_out = torch.empty((shape.B, shape.K), dtype=torch.int32, device=dev) if x_out is None else x_out
-    _need(z_out, "z_out", torch.int32, (shape.B,))
-    _need(x_out, "x_out", torch.int32, (shape.B, shape.K))
+    B, K = shape.B, shape.K
+    z_out = torch.empty(B, dtype=torch.int32, device=dev) if z_out is None else z_out
+    _need(z_out, "z_out", torch.int32, (B,))
+    x_out = z_out.new_empty((B, K)) if x_out is None else x_out
+    _need(x_out, "x_out", torch.int32, (B, K))
     _check(load().dbl_sample_greedy(shape, _ptr(x_hat), _ptr(prior_logits), float(z_temp),
                                     int(seed), int(step), int(seq_offset), _ptr(z_out),
                                     _ptr(x_out), _stream(dev)))
@@ -316,15 +332,7 @@ def dbl_verify_greedy(x_hat, prior_logits, x, logp, z_temp=1.0, seed=0, step=0, 
         raise ValueError("logp must be [B, Kp, V]")
     _need(logp, "logp", torch.float32)
     Kp = logp.shape[1]
-    o = {} if out is None else dict(out)
-    o.setdefault("n_accept", torch.empty(B, dtype=torch.int32, device=dev))
-    o.setdefault("next_token", torch.empty(B, dtype=torch.int32, device=dev))
-    if want_beta:
-        o.setdefault("accept_mass", torch.empty((B, K), dtype=torch.float32, device=dev))
-    if want_al:
-        o.setdefault("al_expected", torch.empty(B, dtype=torch.float32, device=dev))
-    if want_exp_len:
-        o.setdefault("exp_len", torch.empty(B, dtype=torch.float32, device=dev))
+    o = _verify_outputs(out, x_hat, B, K, want_beta, want_al, want_exp_len)
     ws, nws = _workspace(DBL_OP_VERIFY_GREEDY, shape, dev, ws)
     _check(load().dbl_verify_greedy(shape, _ptr(x_hat), _ptr(prior_logits), float(z_temp),
                                     _ptr(x), _ptr(logp), int(Kp), int(seed), int(step),
@@ -344,8 +352,8 @@ def dbl_expected_len_greedy(x_hat, prior_logits, x, logp, z_temp=1.0, want_beta=
     _need(x, "x", torch.int32, (B, K))
     _need(logp, "logp", torch.float32, (B, K, V))
     if want_beta and beta is None:
-        beta = torch.empty((B, K), dtype=torch.float32, device=dev)
-    exp_len = torch.empty(B, dtype=torch.float32, device=dev) if exp_len is None else exp_len
+        beta = x_hat.new_empty((B, K), dtype=torch.float32)
+    exp_len = x_hat.new_empty(B, dtype=torch.float32) if exp_len is None else exp_len
     ws, nws = _workspace(DBL_OP_EXPECTED_LEN_GREEDY, shape, dev, ws)
     _check(load().dbl_expected_len_greedy(shape, _ptr(x_hat), _ptr(prior_logits), float(z_temp),
                                           _ptr(x), _ptr(logp), _ptr(beta), _ptr(exp_len),
@@ -364,12 +372,12 @@ def dbl_acceptance_objective(tls, lmass, lse, prior_logits, x, logp, z_temp=1.0,
     _need(x, "x", torch.int32, (B, K))
     _need(logp, "logp", torch.float32, (B, K, V))
     o = {} if out is None else dict(out)
-    o.setdefault("ell_tau", torch.empty(B, dtype=torch.int32, device=dev))
-    o.setdefault("J", torch.empty(B, dtype=torch.float32, device=dev))
-    o.setdefault("nll", torch.empty(B, dtype=torch.float32, device=dev))
-    if want_terms:
-        o.setdefault("log_r", torch.empty((B, K), dtype=torch.float32, device=dev))
-        o.setdefault("S", torch.empty((B, K), dtype=torch.float32, device=dev))
+    if "ell_tau" not in o:
+        o["ell_tau"] = tls.new_empty(B, dtype=torch.int32)
+    for key, size in (("J", B), ("nll", B), *((("log_r", (B, K)), ("S", (B, K))) if want_terms
+                                              else ())):
+        if key not in o:
+            o[key] = tls.new_empty(size)
     _check(load().dbl_acceptance_objective(shape, _ptr(tls), _ptr(lmass), _ptr(lse),
                                            _ptr(prior_logits), float(z_temp), _ptr(x),
                                            _ptr(logp), float(tau), _ptr(o.get("log_r")),
