@@ -18,6 +18,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "contract.hpp"
 #include "kernels.hpp"
 #include "wave.hpp"
@@ -141,9 +143,11 @@ __global__ __launch_bounds__(64) void greedy_chain_kernel(GreedyArgs a) {
 // K * R <= kGreedyStageKR), one 256-thread workgroup per block. The consistent set at position k
 // depends only on the drafted prefix, so every position is handled at once: lane z of the
 // wavefront holding position k reads whether branch z matched every drafted token before k (a
-// bit mask per branch), normalises pi~ with the same wavefront operations, and forms q at the
-// drafted token and beta_k over the support tokens; one thread then takes E in position order,
-// and wavefront 0 runs the integer accept chain. Bit-identical to greedy_chain_kernel.
+// bit mask per branch), normalises pi~ with the same operations in a segment of lanes (eight
+// positions per wavefront at R <= 8; one position per wavefront at a time took 14.9 us at K = 16,
+// R = 8, this 7.1), and forms q at the drafted token and beta_k over the support tokens; wavefront 1
+// then takes E in position order and wavefront 0 runs the integer accept chain. Bit-identical to
+// greedy_chain_kernel.
 __global__ __launch_bounds__(256) void greedy_chain_parallel_kernel(GreedyArgs a) {
   const BlockArgs& k_ = a.blk;
   const int64_t b = blockIdx.x;
@@ -162,7 +166,6 @@ __global__ __launch_bounds__(256) void greedy_chain_parallel_kernel(GreedyArgs a
   __shared__ float s_pt[kGreedyStageKR];
   __shared__ double s_L0[kMaxR];
   __shared__ uint64_t s_mask[kMaxR];  // bit k: branch z's token is the drafted token at k
-  __shared__ double s_w[kWaves][64];
   __shared__ double s_Q[kGreedyStageK];
   __shared__ double s_P[kGreedyStageK];
   __shared__ double s_beta[kGreedyStageK];
@@ -189,60 +192,83 @@ __global__ __launch_bounds__(256) void greedy_chain_parallel_kernel(GreedyArgs a
   }
   __syncthreads();
   const bool want_beta = a.beta || a.exp_len;
-  for (int k = wave; k < K; k += kWaves) {
-    const uint64_t before = (uint64_t{1} << k) - 1;  // positions 0 .. k - 1 (k < 64)
-    const bool consistent = lane < R && (s_mask[lane] & before) == before;
-    const double w = normalize_weight(consistent ? s_L0[lane] : -INFINITY, R);
-    const int64_t row = (b * k_.K + k) * k_.R;
-    if (lane < R) a.wpost[row + lane] = w;
-    const int32_t xk = s_x[k];
-    const int32_t t = lane < R ? s_t[k * R + lane] : -1;
-    const bool match = lane < R && t == xk;
-    if (!a.trajectory) {
-      double Q = 0.0;
-      for (int z = 0; z < R; ++z) Q = __dadd_rn(Q, lane_f64(match ? w : 0.0, z));
-      const double P = in_vocab(xk, V) ? static_cast<double>(detexp32(s_px[k])) : 0.0;
-      if (lane == 0) {
-        s_Q[k] = Q;
-        s_P[k] = P;
+  // 64 / G positions per wavefront at a time, one segment of G lanes each (lane z = category): each
+  // segment takes the wavefront form's operations in its order.
+  auto positions = [&](auto g_c) {
+    constexpr int G = decltype(g_c)::value, P = 64 / G;
+    const int base = lane & ~(G - 1), z = lane % G;
+    for (int k0 = wave * P; k0 < K; k0 += kWaves * P) {
+      const int k = k0 + lane / G;
+      const bool own = k < K && z < R;
+      const int kc = min(k, K - 1), zc = min(z, R - 1);  // in-bounds indices for every lane
+      const uint64_t before = (uint64_t{1} << kc) - 1;   // positions 0 .. k - 1 (k < 64)
+      const bool consistent = own && (s_mask[zc] & before) == before;
+      const double w = normalize_weight_seg<G>(consistent ? s_L0[zc] : -INFINITY, R);
+      if (own) a.wpost[(b * k_.K + k) * k_.R + z] = w;
+      const int32_t xk = s_x[kc];
+      const int32_t t = own ? s_t[kc * R + zc] : -1;
+      if (!a.trajectory) {
+        const double mw = own && t == xk ? w : 0.0;
+        double Q = 0.0;
+        if constexpr (G <= 16) {  // all shuffles in flight, then the ordered sum
+          double v[G];
+#pragma unroll
+          for (int zz = 0; zz < G; ++zz) v[zz] = __shfl(mw, base + zz);
+#pragma unroll
+          for (int zz = 0; zz < G; ++zz)
+            if (zz < R) Q = __dadd_rn(Q, v[zz]);
+        } else {
+          for (int zz = 0; zz < R; ++zz) Q = __dadd_rn(Q, __shfl(mw, base + zz));
+        }
+        if (own && z == 0) {
+          s_Q[k] = Q;
+          s_P[k] = in_vocab(xk, V) ? static_cast<double>(detexp32(s_px[k])) : 0.0;
+        }
       }
-    }
-    if (want_beta) {
-      s_w[wave][lane] = lane < R ? w : 0.0;
-      // Wavefront-private LDS: the writes above precede these reads in the wavefront's queue.
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      // Lane z represents its token if it is the lowest category with weight on that token;
-      // q(token) is the ascending-z sum of the weights of every category proposing it.
-      double contrib = 0.0;
-      if (lane < R && w > 0.0 && in_vocab(t, V)) {
+      if (want_beta) {
+        // Lane z represents its token if it is the lowest category with weight on that token;
+        // q(token) is the ascending-z sum of the weights of every category proposing it.
         bool first = true;
         double q = 0.0;
-        for (int z = 0; z < R; ++z) {
-          if (s_w[wave][z] > 0.0 && s_t[k * R + z] == t) {
-            if (z < lane) first = false;
-            q = __dadd_rn(q, s_w[wave][z]);
+#pragma unroll
+        for (int zz = 0; zz < (G <= 16 ? G : 64); ++zz) {
+          if (zz >= R) break;
+          const double wz = __shfl(w, base + zz);
+          const int32_t tz = __shfl(t, base + zz);
+          if (wz > 0.0 && tz == t) {
+            first = first && zz >= z;
+            q = __dadd_rn(q, wz);
           }
         }
-        if (first) contrib = fmin(exp(static_cast<double>(s_pt[k * R + lane])), q);
+        double contrib = 0.0;
+        if (own && w > 0.0 && in_vocab(t, V) && first)
+          contrib = fmin(exp(static_cast<double>(s_pt[kc * R + zc])), q);
+#pragma unroll
+        for (int o = G / 2; o > 0; o >>= 1) contrib += __shfl_xor(contrib, o);
+        if (own && z == 0) {
+          s_beta[k] = contrib;
+          if (a.beta) a.beta[b * k_.K + k] = static_cast<float>(contrib);
+        }
       }
-      const double beta_k = wave_sum_f64(contrib);
-      if (lane == 0) {
-        s_beta[k] = beta_k;
-        if (a.beta) a.beta[b * k_.K + k] = static_cast<float>(beta_k);
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     }
-  }
+  };
+  if (R <= 8)
+    positions(std::integral_constant<int, 8>{});
+  else if (R <= 16)
+    positions(std::integral_constant<int, 16>{});
+  else if (R <= 32)
+    positions(std::integral_constant<int, 32>{});
+  else
+    positions(std::integral_constant<int, 64>{});
   __syncthreads();
-  if (tid == 0 && a.exp_len) {
+  if (wave == 1 && a.exp_len) {  // E in position order, beside wavefront 0's accept chain
+    const double bv = s_beta[min(lane, K - 1)];
     double prodB = 1.0, E = 0.0;
     for (int k = 0; k < K; ++k) {
-      prodB *= s_beta[k];
+      prodB *= lane_f64(bv, k);
       E += prodB;
     }
-    a.exp_len[b] = static_cast<float>(E);
+    if (lane == 0) a.exp_len[b] = static_cast<float>(E);
   }
   if (a.trajectory || wave != 0) return;
   // Wavefront 0: every position's accept test at once (the draws do not depend on earlier

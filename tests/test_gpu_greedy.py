@@ -226,3 +226,33 @@ def test_greedy_random_shapes_against_the_oracle():
         _rel_close(out["accept_mass"].cpu().numpy(), ref["beta"])
         _rel_close(out["al_expected"].cpu().numpy(), ref["al"])
         _rel_close(out["exp_len"].cpu().numpy(), ref["E"])
+
+
+# The chain's lane segments: 8, 16, 32 and 64 lanes per position, full and partial, one position, more
+# positions than one round of the four wavefronts takes, and 64 positions (the mask's last bit).
+SEGMENT_EDGES = [(1, 1), (33, 8), (64, 7), (17, 9), (20, 16), (9, 17), (32, 32), (15, 33), (16, 64)]
+
+
+@pytest.mark.parametrize("K,R", SEGMENT_EDGES, ids=[f"k{k}-r{r}" for k, r in SEGMENT_EDGES])
+def test_chain_segments(K, R):
+    """Branches that share the drafted prefix for most of the block, so that consistent sets of every
+    size occur, against the oracle."""
+    from paper_2608_05448_amd import dblast as D
+    rng = np.random.default_rng(1000 * K + R)
+    B, V = 6, 300
+    base = rng.integers(0, V, size=(B, K, 1))
+    x_hat = np.where(rng.random((B, K, R)) < 0.9, base, rng.integers(0, V, size=(B, K, R)))
+    x_hat = x_hat.astype(np.int32)
+    ell = rng.standard_normal((B, R)).astype(np.float32)
+    g = synth.make_uniform_logits((B, K + 1, V), K * 100 + R, scale=2.0)
+    g[:, :K].scatter_add_(-1, torch.from_numpy(base), torch.full((B, K, 1), 9.0, dtype=g.dtype))
+    logp = synth.target_logprobs(g, 1.0)
+    _, x = D.dbl_sample_greedy(torch.from_numpy(x_hat).cuda(), torch.from_numpy(ell).cuda(), V=V)
+    out = D.dbl_verify_greedy(torch.from_numpy(x_hat).cuda(), torch.from_numpy(ell).cuda(), x,
+                              logp.cuda())
+    torch.cuda.synchronize()
+    ref = GR.verify_blocks_greedy(x_hat, ell, 1.0, x.cpu().numpy(), logp.numpy(), 0, 0, np.arange(B))
+    for key, want in (("n_accept", "n_accept"), ("next_token", "next_token")):
+        np.testing.assert_array_equal(out[key].cpu().numpy(), ref[want])
+    for key, want in (("accept_mass", "beta"), ("al_expected", "al"), ("exp_len", "E")):
+        np.testing.assert_allclose(out[key].cpu().numpy(), ref[want], rtol=1e-5, atol=1e-12)
