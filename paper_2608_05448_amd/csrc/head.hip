@@ -1428,17 +1428,24 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerEu) void head_bf16_few_ker
   }
 }
 
-// fp32 path: workgroup (vocabulary tile t, 4 branch rows); thread j owns id 128 t + j.
-constexpr int kF32Rows = 4;
+// fp32 path: workgroup (vocabulary tile t, kF32Rows branch rows); thread j owns id 128 t + j. Bound by
+// latency at the sizes it is for, so every load that can be is in flight at once: the branch rows' chunk
+// (copied one load and one LDS write at a time, 16 in turn, that copy was most of the time: 8 rows at
+// d = 64, V = 256 7.7 -> 6.6 us) and, 32 hidden units at a time, the line of the weight row that the
+// thread alone reads (16-byte loads at any d: global loads need 4-byte alignment only). Sixteen rows per
+// workgroup where that still leaves one per CU and the walk is long enough to pay for the larger
+// reduction: the weight is then read through the caches M / 16 times (128 rows, V = 8000: 45 -> 31 us at
+// d = 256; at d = 100 the step takes 50 us with four rows, 52 with sixteen).
 constexpr int kF32DChunk = 512;
 
+template <int kF32Rows>
 __global__ __launch_bounds__(128) void head_f32_kernel(const float* __restrict__ h,
                                                        const float* __restrict__ w,
                                                        float* __restrict__ tls,
                                                        float* __restrict__ lmass,
                                                        uint64_t* __restrict__ amax, int64_t M,
                                                        int64_t V, int d, int nT) {
-  __shared__ float hs[kF32Rows][kF32DChunk];
+  __shared__ __attribute__((aligned(16))) float hs[kF32Rows][kF32DChunk];
   __shared__ float red[2][kF32Rows];
   __shared__ int redi[2][kF32Rows];
   const int t = blockIdx.x;
@@ -1452,19 +1459,42 @@ __global__ __launch_bounds__(128) void head_f32_kernel(const float* __restrict__
   for (int k0 = 0; k0 < d; k0 += kF32DChunk) {
     const int kn = min(kF32DChunk, d - k0);
     __syncthreads();
-    for (int i = j; i < kF32Rows * kF32DChunk; i += 128) {
-      const int r = i / kF32DChunk, k = i % kF32DChunk;
-      const int64_t m = m0 + r;
-      hs[r][k] = (m < M && k < kn) ? h[m * d + k0 + k] : 0.0f;
-    }
-    __syncthreads();
-    if (valid) {
-      const float* wr = w + v * d + k0;
-      for (int k = 0; k < kn; ++k) {
-        const float wk = wr[k];
+    // The chunk of every row, all loads in flight before the first LDS write (in-bounds addresses:
+    // rows past M and units past the chunk repeat the last one, and count as 0).
+    float x[kF32Rows][kF32DChunk / 128];
 #pragma unroll
-        for (int r = 0; r < kF32Rows; ++r) acc[r] = fmaf(hs[r][k], wk, acc[r]);
-      }
+    for (int r = 0; r < kF32Rows; ++r)
+#pragma unroll
+      for (int i = 0; i < kF32DChunk / 128; ++i)
+        x[r][i] = 128 * i < kn ? h[min(m0 + r, M - 1) * d + k0 + min(j + 128 * i, kn - 1)] : 0.0f;
+#pragma unroll
+    for (int r = 0; r < kF32Rows; ++r)
+#pragma unroll
+      for (int i = 0; i < kF32DChunk / 128; ++i)
+        hs[r][j + 128 * i] = m0 + r < M && j + 128 * i < kn ? x[r][i] : 0.0f;
+    __syncthreads();
+    const float* wr = w + (valid ? v : V - 1) * d + k0;  // ids past V repeat the last row, unused
+    int k = 0;
+    for (; k + 32 <= kn; k += 32) {
+      f32x4u wk[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) wk[i] = *reinterpret_cast<const f32x4u*>(wr + k + 4 * i);
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int r = 0; r < kF32Rows; ++r) {
+          const float4 x = *reinterpret_cast<const float4*>(&hs[r][k + 4 * i]);
+          acc[r] = fmaf(x.x, wk[i][0], acc[r]);
+          acc[r] = fmaf(x.y, wk[i][1], acc[r]);
+          acc[r] = fmaf(x.z, wk[i][2], acc[r]);
+          acc[r] = fmaf(x.w, wk[i][3], acc[r]);
+        }
+    }
+#pragma unroll 4
+    for (; k < kn; ++k) {
+      const float wk = wr[k];
+#pragma unroll
+      for (int r = 0; r < kF32Rows; ++r) acc[r] = fmaf(hs[r][k], wk, acc[r]);
     }
   }
   const int wave = j >> 6;
@@ -1664,11 +1694,18 @@ hipError_t launch_head(const HeadArgs& a, hipStream_t stream) {
                            a.lmass, amax, a.M, a.V, a.d, nT, n_mtiles, vec4);
     }
   } else {
-    const int64_t mblocks = (a.M + kF32Rows - 1) / kF32Rows;
-    if (mblocks > 65535) return hipErrorInvalidConfiguration;
-    hipLaunchKernelGGL(head_f32_kernel, dim3(nT, static_cast<unsigned>(mblocks)), dim3(128), 0,
-                       stream, static_cast<const float*>(a.h), static_cast<const float*>(a.w),
-                       a.tls, a.lmass, amax, a.M, a.V, a.d, nT);
+    const int64_t m16 = (a.M + 15) / 16, m4 = (a.M + 3) / 4;
+    const bool wide = nT * m16 >= 256 && a.d >= 160;
+    if ((wide ? m16 : m4) > 65535) return hipErrorInvalidConfiguration;
+    const dim3 grid(nT, static_cast<unsigned>(wide ? m16 : m4));
+    const float* h = static_cast<const float*>(a.h);
+    const float* w = static_cast<const float*>(a.w);
+    if (wide)
+      hipLaunchKernelGGL(head_f32_kernel<16>, grid, dim3(128), 0, stream, h, w, a.tls, a.lmass, amax,
+                         a.M, a.V, a.d, nT);
+    else
+      hipLaunchKernelGGL(head_f32_kernel<4>, grid, dim3(128), 0, stream, h, w, a.tls, a.lmass, amax,
+                         a.M, a.V, a.d, nT);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -166,3 +166,16 @@ def test_head_few_rows(M, d, V):
         128, dim=1)[:, :V]
     at = lq.gather(1, got[3].view(M, 1).long())[:, 0]
     assert bool((at >= lq.max(1).values - 1e-5).all())
+
+
+# The fp32 head: hidden sizes around one line of 32 units, around one chunk of 512 and in a second,
+# odd multiples (unaligned rows), row counts around the tiles of 4 and 16 rows, and enough tiles for the
+# 16-row form.
+@pytest.mark.parametrize("M,d,V", [
+    (1, 31, 130), (4, 32, 127), (5, 33, 129), (3, 512, 200), (9, 513, 300), (2, 1060, 128),
+    (16, 160, 32769), (17, 161, 16500), (33, 545, 11100),
+])
+def test_head_fp32_edges(M, d, V):
+    h = synth.make_uniform_logits((M, 1, 1, d), 61).to(torch.float32)
+    w = (synth.make_uniform_logits((V, d), 62) / math.sqrt(d)).to(torch.float32)
+    _check(h, w, 2e-5, "fp32-edges")
