@@ -1297,7 +1297,9 @@ __global__ __launch_bounds__(kTopThreads) void filter_topk_share_kernel(FilterAr
   }
 }
 
-__global__ __launch_bounds__(kFT) void filter_topk_merge_kernel(FilterArgs a, int shares) {
+// Eight waves per SIMD, so that two rows share a CU: the fallback's registers spill, the usual path's
+// do not.
+__global__ __launch_bounds__(kFT, 8) void filter_topk_merge_kernel(FilterArgs a, int shares) {
   __shared__ uint64_t hist[256];
   __shared__ uint64_t cand[kCandCap];
   __shared__ int sh_n;
@@ -1370,8 +1372,8 @@ __global__ __launch_bounds__(kFT) void filter_topk_merge_kernel(FilterArgs a, in
 //   6. write    kept ids by comparing logit keys, so only kept ids are divided.
 // The mass pass is bound by its arithmetic (about 50 lane instructions per id for the contract's
 // division and quantised exponential), the others by the row's traffic. 272 rows of 151,936
-// logits at T = 0.7: 27 + 54 + 8 + 25 + 13 + 53 us (189 us per call, 294 with one workgroup per
-// row); 16 rows 41 us (123).
+// logits at T = 0.7: 27 + 54 + 8 + 25 + 10 + 53 us (169 us per call, 276 with one workgroup per
+// row); 16 rows 40 us (123).
 struct NucleusRow {  // a row's workspace: this, seg_max[segs], then the list
   uint64_t bins[kNucBins];
   uint64_t before, tp;
@@ -1524,7 +1526,8 @@ __global__ __launch_bounds__(kSegT) void nucleus_gather_kernel(FilterArgs a, int
   }
 }
 
-__global__ __launch_bounds__(kFT) void nucleus_cut_kernel(FilterArgs a, int segs) {
+// Eight waves per SIMD, so that two rows share a CU (272 rows: 13.1 -> 10.3 us); only the fallback spills.
+__global__ __launch_bounds__(kFT, 8) void nucleus_cut_kernel(FilterArgs a, int segs) {
   __shared__ uint64_t hist[256];
   __shared__ uint64_t nbins[kNucBins];
   __shared__ uint64_t cand[kCandCap];
