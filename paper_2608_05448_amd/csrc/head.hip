@@ -7,9 +7,10 @@
 // reduce in registers plus one cross-half exchange, and the tile-normalised log-probs are
 // stored straight from the accumulators: logits never reach memory. Operand feeds, by hidden
 // size: d % 64 == 0, the 8-wave ping-pong kernel with 64-deep stages copied global -> LDS
-// directly (the main path); d % 32 == 0, 32-deep stages copied global -> LDS by four waves;
-// otherwise a register-staged kernel with padded LDS rows. The branch expander runs a
-// register-staged kernel with 64-deep stages and 128 x 256 tiles.
+// directly (the main path), or up to 128 branch rows the few-row kernel, which streams the weight
+// once; d % 32 == 0, 32-deep stages copied global -> LDS by four waves; otherwise a register-staged
+// kernel with padded LDS rows. The branch expander runs the few-row kernel with tiles by its shape, or
+// a register-staged kernel with 64-deep stages and 128 x 256 tiles.
 //
 // fp32 path: a plain fp32 kernel for fp32 inputs (small problems).
 #include <hip/hip_runtime.h>
@@ -176,7 +177,7 @@ __device__ __forceinline__ void tile_logsoftmax_store(f32x16 (&acc)[NRB][NCB], f
 // its 64 logits per lane are copied out of the accumulators once; in the vocabulary's last,
 // partial tile the ids past V are set to -inf first, so every tile takes the same arithmetic.
 // MASKED: also the whole tiles of a partial 32-row block take the non-temporal stores (with few
-// branch rows that is every tile; the 256-row kernel has no registers to spare for a second form).
+// branch rows that is every tile; in the 256-row kernel the second form cost 1% of the call).
 template <int NRB, int NCB, bool ARG, bool MASKED = false>
 __device__ __forceinline__ void tile_logsoftmax_store_lds(f32x16 (&acc)[NRB][NCB], float* tls,
                                                           float* lmass, uint64_t* amax,
@@ -1151,12 +1152,20 @@ __global__ __launch_bounds__(512, 1) void head_bf16_pp_kernel(
     offB[i] = static_cast<uint32_t>(gb * d * 2 + c * 16);
   }
   const uint32_t lds_row = lds_addr(smem) + (16 * grp + 4 * q) * 1024;
+  // With rows a multiple of 4 KB apart, every XCD starts its tiles' walk over d an eighth after the
+  // previous one's: all of them would otherwise work on the same memory channels at a time, while within
+  // an XCD the tiles that share operand slabs in its L2 stay together (2048 rows at d = 4096 2029 ->
+  // 2008 us; a start per tile instead, as with few rows, breaks the sharing: 6% slower).
+  const int nk = d / C::BK;
+  const int k0 = d % 2048 == 0 ? static_cast<int>(blockIdx.x & 7) * nk / 8 : 0;
   auto copy_A = [&](int s, int slot) {
+    s = s + k0 < nk ? s + k0 : s + k0 - nk;
     const char* base = srcA + static_cast<int64_t>(s) * (2 * C::BK);
 #pragma unroll
     for (int i = 0; i < 4; ++i) lds_dma16(base, offA[i], lds_row + slot * TILE + i * 1024);
   };
   auto copy_B = [&](int s, int slot) {
+    s = s + k0 < nk ? s + k0 : s + k0 - nk;
     const char* base = srcB + static_cast<int64_t>(s) * (2 * C::BK);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -1202,7 +1211,6 @@ __global__ __launch_bounds__(512, 1) void head_bf16_pp_kernel(
                                                                  acc[rb][cb], 0, 0, 0);
   };
 
-  const int nk = d / C::BK;
   const int H = 2 * nk;  // turns per group
   // Turn t of a group: its memory half (fragments of k half t % 2 of stage s = t / 2, plus the
   // turn's copies into slots that stage s - 1 has left), a barrier, its compute half, a barrier.
@@ -1248,11 +1256,9 @@ __global__ __launch_bounds__(512, 1) void head_bf16_pp_kernel(
     a3 = a3 == 2 ? 0 : a3 + 1;
   }
 
-#pragma unroll
-  for (int rb = 0; rb < NRB; ++rb)
-#pragma unroll
-    for (int cb = 0; cb < NCB; ++cb) asm volatile("" : "+a"(acc[rb][cb]));
-
+  // The accumulators stay in the registers they were formed in: at two waves per SIMD all 256 are
+  // addressable, and pinning them to the accumulation file, as before, cost the epilogue 670 moves per
+  // wave (a 512-row head at d = 1024 718 -> 710 us).
   // No memory half reads the slots any more (group 0 passed the barrier closing the last one;
   // group 1 reads none in its last compute half) and every copy has landed, so each wave stages
   // its stores in its own 16 KB of them.
