@@ -276,7 +276,7 @@ __device__ __forceinline__ void beta_body(const VerifyArgs& a, int64_t pos, int 
   if (V >= 4) {
     for (int64_t v = vb + 4 * threadIdx.x; v < ve; v += 4 * blockDim.x) {
       const int tt = static_cast<int>((v - vb) >> 7);
-      const RowGroup g(v, V);
+      const RowGroup g(v, V, (V & 3) != 0);
       const float4 p = g.target(prow);
       float4 x[RT > 0 ? RT : 1];
       float q0 = 0.0f, q1 = 0.0f, q2 = 0.0f, q3 = 0.0f;
@@ -691,7 +691,7 @@ void verify_stream_kernel(VerifyArgs a, int nchunk, int cpw) {
       const int tt = (4 * tid + 1024 * i) >> 7;  // the 32 threads of a half-wave share a tile
       uint64_t sp = 0, sr = 0;
       if (v < ve) {
-        const RowGroup g(v, V);
+        const RowGroup g(v, V, (V & 3) != 0);
         const float4 p = g.target(prow);
         if (!bonus && !res) {
           float q0 = 0.0f, q1 = 0.0f, q2 = 0.0f, q3 = 0.0f;
@@ -810,7 +810,7 @@ __global__ __launch_bounds__(1024) void verify_stream_wide_kernel(VerifyArgs a, 
   const int nt = min(TPC, k_.nT - t0);
   const int tt = tid >> 5;  // the 32 threads of a half-wave share a tile
   // Threads past the row repeat its last group with every target value masked.
-  const RowGroup g(static_cast<int64_t>(t0) * kTile + 4 * tid, V);
+  const RowGroup g(static_cast<int64_t>(t0) * kTile + 4 * tid, V, true);
   const float* prow = a.logp + (b * a.Kp + k) * V;
   const float* trow = k_.tls + m0 * V;
   float4 p = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
