@@ -1702,7 +1702,7 @@ hipError_t launch_head(const HeadArgs& a, hipStream_t stream) {
   } else {
     const int64_t m16 = (a.M + 15) / 16, m4 = (a.M + 3) / 4;
     const bool wide = nT * m16 >= 256 && a.d >= 160;
-    if ((wide ? m16 : m4) > 65535) return hipErrorInvalidConfiguration;
+    if (m4 > 65535) return hipErrorInvalidConfiguration;
     const dim3 grid(nT, static_cast<unsigned>(wide ? m16 : m4));
     const float* h = static_cast<const float*>(a.h);
     const float* w = static_cast<const float*>(a.w);

@@ -1668,7 +1668,7 @@ __global__ __launch_bounds__(kFT) void determinism_mean_kernel(DeterminismArgs a
 }  // namespace
 
 hipError_t launch_filter(const FilterArgs& a, hipStream_t stream) {
-  if (a.N > 0x7fffffff) return hipErrorInvalidConfiguration;
+  if (a.N > 0x7fffffff / 4) return hipErrorInvalidConfiguration;
   const dim3 rows(static_cast<unsigned>(a.N));
   const bool k_off = a.top_k == 0 || a.top_k >= a.V;
   const bool nucleus = a.temperature > 0.0f && k_off && a.top_p < 1.0f;
