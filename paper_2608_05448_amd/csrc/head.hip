@@ -499,6 +499,24 @@ __global__ __launch_bounds__(C::kThreads, 1) void head_bf16_kernel(
                                              m0 + wm * C::TM, lane, vec4);
 }
 
+// Every kernel that can serve a shape adds a row's products in the same order, 16 hidden units at a
+// time, so that a row's result depends neither on the other rows of the call nor on its place among
+// them. The sum starts at unit walk_start, runs to d and wraps around. It starts at 0 unless the operand
+// rows are a multiple of 4 KB apart: workgroups that walk such rows from the same unit all load from the
+// same few memory channels, so each group of weight rows starts 640 units after the one before it. The
+// expander takes groups of 1024 rows (15 trunk rows against 32768 x 4096 56 -> 40 us, 128 rows 61 -> 56;
+// with 4096 41). The head takes 4096: 8, 60 and 120 rows against 151936 x 4096 229, 238 and 258 ->
+// 213, 218 and 242 us, while the 256-row kernel, whose tiles share operand slabs in the L2 only as long as
+// they walk together, is 0.5% slower than from 0 (1.3% with 2048, 2% with 1024). A start is a multiple
+// of 128 units, the deepest stage of any kernel.
+constexpr int kWalkExpand = 1024;
+constexpr int kWalkHead = 4096;
+template <bool EXPAND>
+__device__ __forceinline__ int walk_start(int64_t v0, int d) {
+  return d % 2048 == 0 ? 128 * (5 * static_cast<int>(v0 / (EXPAND ? kWalkExpand : kWalkHead)) % (d / 128))
+                       : 0;
+}
+
 // ---------------------------------------------------------------------------------------
 // Direct-to-LDS variant (hidden sizes that are a multiple of BK): operand tiles are copied
 // global -> LDS by global_load_lds_dwordx4 into an S-stage ring, issued S - 1 stages ahead, so
@@ -745,11 +763,16 @@ __global__ __launch_bounds__(C::kThreads, C::kWgPerCu) void head_bf16_dma_kernel
   // its own operands.
 
   const int nk = d / C::BK;
+  const int first = EPI == kEpiExpand ? walk_start<true>(v0, d) / C::BK : 0;  // the head's d is no multiple of 64
+  auto stage_at = [&](int s) {
+    if constexpr (EPI != kEpiExpand) return s;
+    return s + first < nk ? s + first : s + first - nk;
+  };
   // Prologue: stages 0 .. S-2 in flight, stage 0 visible, its first-k-step fragments loaded.
   // (Stages past nk - 1 repeat stage nk - 1 into unused slots.)
 #pragma unroll
   for (int j = 0; j < C::S - 1; ++j) {
-    const int kj = min(j, nk - 1) * C::BK;
+    const int kj = stage_at(min(j, nk - 1)) * C::BK;
 #pragma unroll
     for (int i = 0; i < C::PER_STAGE; ++i) {
       if (j == 0) issue_one(std::integral_constant<int, 0>{}, kj, i);
@@ -776,7 +799,7 @@ __global__ __launch_bounds__(C::kThreads, C::kWgPerCu) void head_bf16_dma_kernel
     // Stage kt + S - 1 goes to the slot of stage kt - 1, which every wave has finished reading.
     // Past the last stage the copy is repeated from stage nk - 1 into that free slot: the loads
     // stay unconditional, so the outstanding count per wave is always S - 2 stages.
-    const int kd = min(kt + C::S - 1, nk - 1) * C::BK;
+    const int kd = stage_at(min(kt + C::S - 1, nk - 1)) * C::BK;
 #pragma unroll
     for (int st = 0; st < KS; ++st) {
       const int cur = st & 1;
@@ -835,13 +858,6 @@ __global__ __launch_bounds__(C::kThreads, C::kWgPerCu) void head_bf16_dma_kernel
         acc, ea.tls, ea.lmass, ea.amax, M, V, ea.nT, v0w, m0 + wm * C::TM, lane, ea.vec4);
 }
 
-
-// Stages between the starting points of consecutive weight tiles: where a workgroup streams weight
-// rows whose stride is a multiple of 4 KB (d = 2048, 4096) alone, all workgroups would walk the same
-// few memory channels together if they started at the same hidden unit. Each starts its walk over d
-// kRotate stages after its neighbour and wraps around: 128 rows against a 32768 x 4096 weight
-// 69 -> 60 us, 15 rows 66 -> 50; at d = 2560 1-2%.
-constexpr int kRotate = 5;
 
 // ---------------------------------------------------------------------------------------
 // Register-staged kernel (the expander's GEMM, hidden sizes that are a multiple of 64; it was
@@ -955,7 +971,7 @@ __global__ __launch_bounds__(C::kThreads, 1) void head_bf16_rs_kernel(
                                                             acc[rb_][cb], 0, 0, 0);
   };
   const int nk = d / BK;
-  const int k0 = kRotate * vt % nk;
+  const int k0 = walk_start<EPI == kEpiExpand>(v0, d) / BK;
   // global -> registers (stage s, clamped to the last stage) and registers -> LDS, one 16-byte
   // load of one operand at a time (q < LDA: w, else h)
   // Stages past the last (the pipeline's final three reloads) read the tile's first 16 bytes in
@@ -1152,12 +1168,8 @@ __global__ __launch_bounds__(512, 1) void head_bf16_pp_kernel(
     offB[i] = static_cast<uint32_t>(gb * d * 2 + c * 16);
   }
   const uint32_t lds_row = lds_addr(smem) + (16 * grp + 4 * q) * 1024;
-  // With rows a multiple of 4 KB apart, every XCD starts its tiles' walk over d an eighth after the
-  // previous one's: all of them would otherwise work on the same memory channels at a time, while within
-  // an XCD the tiles that share operand slabs in its L2 stay together (2048 rows at d = 4096 2029 ->
-  // 2008 us; a start per tile instead, as with few rows, breaks the sharing: 6% slower).
   const int nk = d / C::BK;
-  const int k0 = d % 2048 == 0 ? static_cast<int>(blockIdx.x & 7) * nk / 8 : 0;
+  const int k0 = walk_start<false>(v0, d) / C::BK;
   auto copy_A = [&](int s, int slot) {
     s = s + k0 < nk ? s + k0 : s + k0 - nk;
     const char* base = srcA + static_cast<int64_t>(s) * (2 * C::BK);
@@ -1273,27 +1285,27 @@ __global__ __launch_bounds__(512, 1) void head_bf16_pp_kernel(
 // streamed once, so HBM bounds the call, and what matters is that every CU has enough of it in
 // flight and that no CU idles. A workgroup of WV x WM x WK waves owns BV weight rows and BM branch
 // rows; each stage is KB 64-deep blocks of both, copied global -> LDS (128-byte row segments) into
-// an S-slot ring, S - 1 stages ahead, with one barrier per stage. The WK waves of a tile take every
-// WK-th 16-deep k step and their sums are added in order through LDS at the end. The weight's copies
-// are non-temporal (head, 15 rows at d = 2560: 150 -> 133 us): nothing reads it again.
-template <int BV_, int BM_, int WV_, int WM_, int WK_, int KB_, int S_>
+// an S-slot ring, S - 1 stages ahead, with one barrier per stage. The weight's copies are
+// non-temporal, also where several row tiles read the same weight tile (they walk it together on one
+// XCD): with caches that hold other data, as between two steps, 128 rows against 10240 x 2560 take 30 us
+// and 40 with plain copies, 256 rows 37 and 48, 60 rows against 32768 x 4096 47 and 106.
+template <int BV_, int BM_, int WV_, int WM_, int KB_, int S_>
 struct FewCfg {
-  static constexpr int BV = BV_, BM = BM_, WV = WV_, WM = WM_, WK = WK_, KB = KB_, S = S_;
-  static constexpr int NW = WV * WM * WK, kThreads = 64 * NW;
+  static constexpr int BV = BV_, BM = BM_, WV = WV_, WM = WM_, KB = KB_, S = S_;
+  static constexpr int NW = WV * WM, kThreads = 64 * NW;
   static constexpr int TV = BV / WV, TM = BM / WM, NRB = TV / 32, NCB = TM / 32;
   static constexpr int ROWB = 128;                          // bytes per LDS row: 64 bf16
   static constexpr int BLK = (BV + BM) * ROWB;              // bytes per 64-deep block
   static constexpr int STAGE = KB * BLK;
   static constexpr int PER = KB * (BV + BM) / 8 / NW;       // 8-row copies per wave and stage
-  static constexpr int KSTEPS = 4 * KB / WK;                // 16-deep k steps per wave and stage
+  static constexpr int KSTEPS = 4 * KB;                     // 16-deep k steps per stage
   static constexpr int kLds = S * STAGE;
   static constexpr int kWgPerCu = 160 * 1024 / kLds;
   static constexpr int kWavesPerEu = kWgPerCu * NW < 8 ? 1 : kWgPerCu * NW < 16 ? 2 : 4;
-  static_assert(TV % 32 == 0 && TM % 32 == 0 && 4 * KB % WK == 0, "tiling");
+  static_assert(TV % 32 == 0 && TM % 32 == 0, "tiling");
   static_assert(BV / 8 % NW == 0 && BM / 8 % NW == 0, "whole row groups per wave");
   static_assert(S >= 2 && (S - 1) * PER <= 63, "ring depth and vmcnt range");
   static_assert(kLds <= 160 * 1024, "LDS per CU");
-  static_assert((WK - 1) * WV * WM * TV * TM * 4 <= kLds, "partial sums fit the ring");
 };
 
 template <class C, int EPI>
@@ -1305,9 +1317,8 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerEu) void head_bf16_few_ker
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wk = wave % C::WK;
-  const int wm = wave / C::WK % C::WM;
-  const int wv = wave / C::WK / C::WM;
+  const int wm = wave % C::WM;
+  const int wv = wave / C::WM;
   int vt, mt;
   tile_of(xcd_remap(blockIdx.x, gridDim.x), gridDim.x / n_mtiles, n_mtiles, &vt, &mt);
   const int64_t v0 = static_cast<int64_t>(vt) * C::BV;
@@ -1334,7 +1345,7 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerEu) void head_bf16_few_ker
   }
   const uint32_t lds0 = lds_addr(smem);
   const int nk = d / (64 * C::KB);
-  const int r0 = kRotate * vt % nk;
+  const int r0 = walk_start<EPI == kEpiExpand>(v0, d) / (64 * C::KB);
   auto copy = [&](int s, int slot) {
     s = s + r0 < nk ? s + r0 : s + r0 - nk;
     const uint32_t to = lds0 + slot * C::STAGE;
@@ -1379,8 +1390,7 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerEu) void head_bf16_few_ker
     if (kt + C::S - 1 < nk) copy(kt + C::S - 1, slot == 0 ? C::S - 1 : slot - 1);
     const char* base = smem + slot * C::STAGE;
 #pragma unroll
-    for (int j = 0; j < C::KSTEPS; ++j) {
-      const int ks = j * C::WK + wk;  // 16-deep k step of the stage
+    for (int ks = 0; ks < C::KSTEPS; ++ks) {
       const char* blk = base + (ks >> 2) * C::BLK;
       const int x = (32 * (ks & 3)) ^ tt;
       bf16x8 af[NRB], bfr[NCB];
@@ -1402,25 +1412,6 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerEu) void head_bf16_few_ker
   __builtin_amdgcn_s_barrier();  // the ring is free: nothing reads it, every copy has landed
   asm volatile("" ::: "memory");
 
-  if constexpr (C::WK > 1) {
-    f32x16* part = reinterpret_cast<f32x16*>(smem);
-    constexpr int PT = NRB * NCB * 64;  // 16-register groups per wave tile
-    if (wk > 0) {
-#pragma unroll
-      for (int i = 0; i < NRB * NCB; ++i)
-        part[((wk - 1) * C::WV * C::WM + wv * C::WM + wm) * PT + i * 64 + lane] = acc[i / NCB][i % NCB];
-    }
-    __syncthreads();
-    if (wk == 0) {
-#pragma unroll
-      for (int p = 0; p < C::WK - 1; ++p)
-#pragma unroll
-        for (int i = 0; i < NRB * NCB; ++i)
-          acc[i / NCB][i % NCB] += part[(p * C::WV * C::WM + wv * C::WM + wm) * PT + i * 64 + lane];
-    }
-    __syncthreads();  // the epilogue stages its stores where the partial sums were
-    if (wk > 0) return;
-  }
   const int64_t v0w = v0 + wv * C::TV;
   if (v0w >= V) return;
   if constexpr (EPI == kEpiExpand) {
@@ -1601,11 +1592,11 @@ __global__ __launch_bounds__(256) void lse_finalize_kernel(const float* __restri
   }
 }
 
-// The head's tiles: two workgroups per CU of four waves, the 64 rows over two of them and the k steps
-// over two (up to 32 rows 135 us at d = 2560, where one wave per 32 rows took 149); above 64 rows one
-// workgroup of eight waves over 256 weight rows.
-using HeadFew64 = FewCfg<128, 64, 1, 2, 2, 1, 3>;
-using HeadFew128 = FewCfg<256, 128, 2, 4, 1, 1, 3>;
+// The head's tiles: one workgroup per CU over 256 weight rows, of four waves for up to 64 branch rows
+// (60 rows at d = 2560 149 us, where two workgroups of two waves over 128 weight rows took 160) and of
+// eight above.
+using HeadFew64 = FewCfg<256, 64, 2, 2, 1, 3>;
+using HeadFew128 = FewCfg<256, 128, 2, 4, 1, 3>;
 
 template <class C, int EPI>
 hipError_t launch_few(const __bf16* h, const __bf16* w, const EpiArgs& ea, int64_t M, int64_t V,
@@ -1640,9 +1631,9 @@ hipError_t launch_head(const HeadArgs& a, hipStream_t stream) {
     const __bf16* h = static_cast<const __bf16*>(a.h);
     const __bf16* w = static_cast<const __bf16*>(a.w);
     // Up to 128 rows the weight's stream bounds the call and a 256-row tile would be mostly padding.
-    // V = 151,936, with the LSE launch: 60 rows at d = 2560 199 -> 152 us, 128 rows 205 -> 178, 60 rows
-    // at d = 4096 299 -> 214, 120 rows 312 -> 249; from 129 rows on two 128-row tiles would stream the weight twice (180 rows at d = 2560 264 us against
-    // the ping-pong kernel's 215).
+    // V = 151,936, with the LSE launch: 60 rows at d = 2560 203 -> 149 us, 120 rows 212 -> 176, 60 rows
+    // at d = 4096 300 -> 217, 120 rows 306 -> 242; from 129 rows on two 128-row tiles would stream the
+    // weight twice (180 rows at d = 2560 264 us against the ping-pong kernel's 215).
     if (a.d % 64 == 0 && a.M <= 128) {
       EpiArgs ea{};
       ea.tls = a.tls;
@@ -1820,10 +1811,10 @@ hipError_t launch_expand_few(const ExpandArgs& a, int64_t N, hipStream_t stream)
                                    static_cast<const __bf16*>(a.W), ea, a.M, N, a.d, stream);
 }
 
-using Few128x128 = FewCfg<128, 128, 2, 4, 1, 1, 4>;
-using Few128x64 = FewCfg<128, 64, 2, 2, 1, 1, 3>;
-using Few64x64 = FewCfg<64, 64, 2, 2, 1, 1, 4>;
-using Few64x32 = FewCfg<64, 32, 2, 1, 2, 2, 4>;
+using Few128x128 = FewCfg<128, 128, 2, 4, 1, 4>;
+using Few128x64 = FewCfg<128, 64, 2, 2, 1, 3>;
+using Few64x64 = FewCfg<64, 64, 2, 2, 1, 4>;
+using Few64x32 = FewCfg<64, 32, 2, 1, 2, 4>;
 
 hipError_t launch_expand(const ExpandArgs& a, hipStream_t stream) {
   const int64_t N = a.R * a.d;

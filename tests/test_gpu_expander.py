@@ -157,3 +157,21 @@ EXPAND_EDGES = [
 @pytest.mark.parametrize("case", EXPAND_EDGES, ids=[c[0] for c in EXPAND_EDGES])
 def test_expander_edges(case):
     _expander_case(*case)
+
+
+# A trunk row's branch states do not depend on the other rows of the call: row counts that take every
+# tile, up to the 256 x 256 ones, at hidden sizes whose sum starts at 0 (128, 192) and, from the second
+# group of 1024 features on, further on (2048).
+@pytest.mark.parametrize("R,d", [(48, 128), (32, 192), (3, 2048)])
+def test_expander_rows_do_not_depend_on_the_batch(R, d):
+    from paper_2608_05448_amd import dblast as D
+    M = 2900
+    h = synth.make_uniform_logits((1, M, d), 81).to(torch.bfloat16).cuda()
+    W = (synth.make_uniform_logits((R * d, d), 82) * (0.5 / d ** 0.5)).to(torch.bfloat16).cuda()
+    c = (synth.make_uniform_logits((R * d,), 83) * 0.1).to(torch.bfloat16).cuda()
+    whole = D.dbl_expand_branches(h, W, c, R)
+    for lo, n in ((5, 1), (0, 32), (9, 33), (64, 64), (70, 65), (0, 128), (33, 129), (300, 256),
+                  (1000, 700)):
+        print(f"[expander] R={R} d={d} rows {lo}..{lo + n} alone", flush=True)
+        part = D.dbl_expand_branches(h[:, lo:lo + n].contiguous(), W, c, R)
+        assert torch.equal(whole[:, lo:lo + n], part), (R, d, lo, n)

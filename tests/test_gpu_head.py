@@ -179,3 +179,26 @@ def test_head_fp32_edges(M, d, V):
     h = synth.make_uniform_logits((M, 1, 1, d), 61).to(torch.float32)
     w = (synth.make_uniform_logits((V, d), 62) / math.sqrt(d)).to(torch.float32)
     _check(h, w, 2e-5, "fp32-edges")
+
+
+# A row's log-probabilities depend neither on the other rows of the call nor on its place among them:
+# sharding a batch, or drafting one sequence of it alone, draws the same tokens. Row counts on both sides
+# of every change of kernel and tile, hidden sizes whose sum starts at 0 and, in the second group of 4096
+# ids, further on.
+@pytest.mark.parametrize("d", [64, 320, 2048, 4096])
+def test_head_rows_do_not_depend_on_the_batch(d):
+    from paper_2608_05448_amd import dblast as D
+    M, V = 2100, 5003
+    h = synth.make_uniform_logits((M, 1, 1, d), 71).to(torch.bfloat16)
+    h[1500] = h[3]
+    w = (synth.make_uniform_logits((V, d), 72) * (2.0 / math.sqrt(d))).to(torch.bfloat16)
+    hd, wd = h.cuda(), w.cuda()
+    whole = D.dbl_head_logprobs(hd, wd, argmax=True)
+    for out in whole:
+        assert torch.equal(out[1500], out[3]), d
+    for lo, n in ((3, 1), (0, 32), (40, 33), (7, 64), (100, 65), (0, 128), (50, 129), (600, 257),
+                  (1000, 1100)):
+        print(f"[head] d={d} rows {lo}..{lo + n} alone", flush=True)
+        part = D.dbl_head_logprobs(hd[lo:lo + n].contiguous(), wd, argmax=True)
+        for a, b in zip(whole, part):
+            assert torch.equal(a[lo:lo + n], b), (d, lo, n)
