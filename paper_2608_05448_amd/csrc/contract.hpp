@@ -89,6 +89,26 @@ __device__ __forceinline__ float detexp32(float x) {
   return ldexpf(p, static_cast<int>(n));
 }
 
+// detexp32 without its early return, for lanes that would diverge there: the same value for every x.
+__device__ __forceinline__ float detexp32_flat(float x) {
+#pragma clang fp contract(off)
+  const float c = fminf(fmaxf(x, -100.0f), 0.0f);
+  constexpr float kLog2e = 0x1.715476p+0f;
+  constexpr float kLn2Hi = 0x1.62e4p-1f;
+  constexpr float kLn2Lo = 0x1.7f7d1cp-20f;
+  const float n = rintf(__fmul_rn(c, kLog2e));
+  const float r = __fsub_rn(__fsub_rn(c, __fmul_rn(n, kLn2Hi)), __fmul_rn(n, kLn2Lo));
+  float p = static_cast<float>(1.0 / 5040.0);
+  p = __fadd_rn(__fmul_rn(p, r), static_cast<float>(1.0 / 720.0));
+  p = __fadd_rn(__fmul_rn(p, r), static_cast<float>(1.0 / 120.0));
+  p = __fadd_rn(__fmul_rn(p, r), static_cast<float>(1.0 / 24.0));
+  p = __fadd_rn(__fmul_rn(p, r), static_cast<float>(1.0 / 6.0));
+  p = __fadd_rn(__fmul_rn(p, r), 0.5f);
+  p = __fadd_rn(__fmul_rn(p, r), 1.0f);
+  p = __fadd_rn(__fmul_rn(p, r), 1.0f);
+  return x > -80.0f ? ldexpf(p, static_cast<int>(n)) : 0.0f;
+}
+
 // binary64: for category weights. Inputs above 0 are clamped to 0; below -708, -inf and NaN
 // give 0.
 __device__ __forceinline__ double dexp64(double x) {

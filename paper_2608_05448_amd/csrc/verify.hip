@@ -782,16 +782,24 @@ void verify_stream_kernel(VerifyArgs a, int nchunk, int cpw) {
 }
 
 // The same work where the whole grid fits the chip at once (one or a few sequences, short
-// vocabularies): latency bounds it, so 1024 threads take a chunk of 32 tiles in one step. The chunk's
-// loads are issued before anything else (the tile offsets and weights arrive meanwhile), and at the
-// first rejected position every branch row is in flight at once, where the kernel above walks the
-// categories with one load each: that walk, four steps long, was most of its time (one sequence, K = 15,
-// R = 4: 22 -> 13 us; K = 16, R = 8 the call 55 -> 31).
+// vocabularies): latency bounds it, so 1024 threads take a chunk in one step (32 tiles, R <= 4) or one
+// and a quarter (40 tiles). The first step's loads are issued before anything else (the tile offsets
+// and weights arrive meanwhile), and at the first rejected position every branch row is in flight at
+// once, where the kernel above walks the categories with one load each: that walk, four steps long, was
+// most of its time. Its exponential has no early return (four lanes' worth of divergent branches per
+// category held 46 more registers than there are at R = 8). The chunks and the order of the
+// acceptance-mass sums are those of the kernel above (each group's sum goes through LDS to the thread that
+// adds it there), so that a block's results do not depend on how many blocks share the launch. One
+// sequence, K = 15: 34 -> 22 us per call at R = 4, 55 -> 29 at R = 8.
+constexpr int kWideThreads = 1024;
+
 template <int RT>
-__global__ __launch_bounds__(1024) void verify_stream_wide_kernel(VerifyArgs a, int nchunk) {
-  constexpr int TPC = kTilesPerChunk;
+__global__ __launch_bounds__(kWideThreads) void verify_stream_wide_kernel(VerifyArgs a, int nchunk) {
+  constexpr int TPC = stream_tiles(RT);
+  constexpr int kGroups = TPC * kTile / 4;  // of four ids in a chunk
+  constexpr int kSteps = (kGroups + kWideThreads - 1) / kWideThreads;
   constexpr int ZB = RT > 0 ? RT : 8;  // categories whose loads are in flight together
-  static_assert(TPC * kTile == 4 * 1024, "four ids per thread");
+  static_assert(kGroups % 256 == 0 && kGroups >= kWideThreads, "whole steps of the kernel above");
   const BlockArgs& k_ = a.blk;
   const int64_t B = k_.B;
   const int c = static_cast<int>(blockIdx.x % static_cast<unsigned>(nchunk));
@@ -803,26 +811,27 @@ __global__ __launch_bounds__(1024) void verify_stream_wide_kernel(VerifyArgs a, 
   __shared__ float s_w[kMaxR];
   __shared__ double s_wz[kMaxR];
   __shared__ float s_offx[kMaxR][TPC];  // fl32(lmass - lse) of the chunk's tiles
-  __shared__ float red[16];
+  __shared__ float s_sum[kGroups];      // acceptance mass of each group
+  __shared__ float red[4];
   const bool bonus = k == k_.K;
   const int64_t m0 = (b * k_.K + k) * k_.R;  // first branch row of the position (k < K)
   const int t0 = c * TPC;
   const int nt = min(TPC, k_.nT - t0);
-  const int tt = tid >> 5;  // the 32 threads of a half-wave share a tile
-  // Threads past the row repeat its last group with every target value masked.
-  const RowGroup g(static_cast<int64_t>(t0) * kTile + 4 * tid, V, true);
   const float* prow = a.logp + (b * a.Kp + k) * V;
   const float* trow = k_.tls + m0 * V;
+  // Groups past the row repeat its last one with every target value masked.
+  auto group = [&](int i) { return RowGroup(static_cast<int64_t>(t0) * kTile + 4 * i, V, true); };
   float4 p = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
   float4 x[ZB];
-  auto load_rows = [&](int z0) {
+  auto load_rows = [&](const RowGroup& g, int z0) {
 #pragma unroll
     for (int z = 0; z < ZB; ++z) x[z] = g.branch(trow + min(z0 + z, R - 1) * V);
   };
   if (!bonus) {
+    const RowGroup g = group(tid);
     p = g.target(prow);
-    load_rows(0);
-    for (int i = tid; i < R * TPC; i += 1024) {
+    load_rows(g, 0);
+    for (int i = tid; i < R * TPC; i += kWideThreads) {
       const int z = i / TPC, t = i % TPC;
       if (t < nt) s_offx[z][t] = k_.lmass[(m0 + z) * k_.nT + t0 + t] - k_.lse[m0 + z];
     }
@@ -836,45 +845,52 @@ __global__ __launch_bounds__(1024) void verify_stream_wide_kernel(VerifyArgs a, 
   __syncthreads();
   const bool res = bonus ? ks == k_.K : k == ks;
   if (bonus && !res) return;  // workgroup-uniform
-  uint64_t sp = 0, sr = 0;
-  if (bonus) p = g.target(prow);
-  const float pe[4] = {p.x, p.y, p.z, p.w};
-  if (!bonus) {
-    float q[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 1
+  for (int step = 0; step < kSteps; ++step) {
+    const int i = tid + step * kWideThreads;
+    if (step > 0 && i >= kGroups) break;  // whole wavefronts
+    const RowGroup g = group(i);
+    const int tt = i >> 5;  // the 32 threads of a half-wave share a tile
+    if (bonus || step > 0) p = g.target(prow);
+    const float pe[4] = {p.x, p.y, p.z, p.w};
     double Q[4] = {0.0, 0.0, 0.0, 0.0};
-    for (int z0 = 0; z0 < R; z0 += ZB) {
-      if (z0 > 0) load_rows(z0);
-#pragma unroll
-      for (int z = 0; z < ZB; ++z) {
-        if (RT == 0 && z0 + z >= R) break;
-        const float xe[4] = {x[z].x, x[z].y, x[z].z, x[z].w};
-        const float o = s_offx[z0 + z][tt] * kLog2eChunk, w = s_w[z0 + z];
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          q[e] = fmaf(w, __builtin_amdgcn_exp2f(fmaf(xe[e], kLog2eChunk, o)), q[e]);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      if (res) {
+    if (!bonus) {
+      float q[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      for (int z0 = 0; z0 < R; z0 += ZB) {
+        if (z0 > 0 || step > 0) load_rows(g, z0);
 #pragma unroll
         for (int z = 0; z < ZB; ++z) {
           if (RT == 0 && z0 + z >= R) break;
           const float xe[4] = {x[z].x, x[z].y, x[z].z, x[z].w};
-          const float oz = s_offx[z0 + z][tt];
-          const double wz = s_wz[z0 + z];
+          const float o = s_offx[z0 + z][tt] * kLog2eChunk, w = s_w[z0 + z];
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            Q[e] = __dadd_rn(Q[e], __dmul_rn(wz, static_cast<double>(detexp32(__fadd_rn(xe[e], oz)))));
-          __builtin_amdgcn_sched_barrier(0);  // one category's temporaries at a time
+            q[e] = fmaf(w, __builtin_amdgcn_exp2f(fmaf(xe[e], kLog2eChunk, o)), q[e]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+        if (res) {
+#pragma unroll
+          for (int z = 0; z < ZB; ++z) {
+            if (RT == 0 && z0 + z >= R) break;
+            const float xe[4] = {x[z].x, x[z].y, x[z].z, x[z].w};
+            const float oz = s_offx[z0 + z][tt];
+            const double wz = s_wz[z0 + z];
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+              Q[e] = __dadd_rn(
+                  Q[e], __dmul_rn(wz, static_cast<double>(detexp32_flat(__fadd_rn(xe[e], oz)))));
+            __builtin_amdgcn_sched_barrier(0);  // one category's temporaries at a time
+          }
         }
       }
+      const float s = fminf(__builtin_amdgcn_exp2f(pe[0] * kLog2eChunk), q[0]) +
+                      fminf(__builtin_amdgcn_exp2f(pe[1] * kLog2eChunk), q[1]) +
+                      fminf(__builtin_amdgcn_exp2f(pe[2] * kLog2eChunk), q[2]) +
+                      fminf(__builtin_amdgcn_exp2f(pe[3] * kLog2eChunk), q[3]);
+      s_sum[i] = tt < nt ? s : 0.0f;  // past the row's tiles the offsets are not set
     }
-    float acc = 0.0f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) acc += fminf(__builtin_amdgcn_exp2f(pe[e] * kLog2eChunk), q[e]);
-    if (tt >= nt) acc = 0.0f;  // past the row's tiles the offsets are not set
-    acc = wave_sum_f32(acc);
-    if ((tid & 63) == 0) red[tid >> 6] = acc;
-    if (res)
+    if (res) {
+      uint64_t sp = 0, sr = 0;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const uint64_t P = quant_detexp32(pe[e]);
@@ -882,36 +898,38 @@ __global__ __launch_bounds__(1024) void verify_stream_wide_kernel(VerifyArgs a, 
         sr += P > Qi ? P - Qi : 0;
         sp += P;
       }
-    __syncthreads();
-    if (tid < 64) {
-      float s = tid < 16 ? red[tid] : 0.0f;
 #pragma unroll
-      for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o);
-      if (tid == 0) a.beta_part[(b * k_.K + k) * nchunk + c] = s;
-    }
-  } else {  // the bonus row after full acceptance: P only
-#pragma unroll
-    for (int e = 0; e < 4; ++e) sp += quant_detexp32(pe[e]);
-  }
-  if (res) {
-#pragma unroll
-    for (int o = 16; o > 0; o >>= 1) {
-      sp += __shfl_xor(sp, o);
-      sr += __shfl_xor(sr, o);
-    }
-    if ((tid & 31) == 0 && tt < nt) {
-      a.p_tiles[b * k_.nT + t0 + tt] = sp;
-      if (!bonus) a.res_tiles[b * k_.nT + t0 + tt] = sr;
+      for (int o = 16; o > 0; o >>= 1) {
+        sp += __shfl_xor(sp, o);
+        sr += __shfl_xor(sr, o);
+      }
+      if ((tid & 31) == 0 && tt < nt) {
+        a.p_tiles[b * k_.nT + t0 + tt] = sp;
+        if (!bonus) a.res_tiles[b * k_.nT + t0 + tt] = sr;
+      }
     }
   }
+  if (bonus) return;
+  __syncthreads();
+  if (tid < 256) {  // the kernel above: thread t adds groups t, t + 256, ... in turn
+    float acc = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kGroups / 256; ++i) acc += s_sum[tid + 256 * i];
+    acc = wave_sum_f32(acc);
+    if ((tid & 63) == 0) red[tid >> 6] = acc;
+  }
+  __syncthreads();
+  if (tid == 0)
+    a.beta_part[(b * k_.K + k) * nchunk + c] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 }  // namespace
 
-// Grids up to this many 1024-thread workgroups take the wide stream kernel. Whole calls with the bonus
-// row, 256 threads against 1024: 608 workgroups (K = 15, R = 4) 33 and 27 us, 1216 (two sequences) 37
-// and 33, 1254 (three sequences, K = 10, R = 8) 62 and 46, 1824 43 and 44, 2432 (R = 2) 33 and 35, 3040
-// 51 and 61. A row of up to eight tiles is one step of 256 threads already.
+// Grids up to this many chunks of 32 tiles take the wide stream kernel. Whole calls with the bonus row,
+// 256 threads against 1024: 608 chunks (K = 15, R = 4) 34 and 22 us, 684 (two sequences, R = 8) 55 and 32,
+// 1254 (three sequences, K = 10) 62 and 43 at R = 8 and 28 and 24 at R = 2; above, before the residual
+// went branch-free, 1824 43 and 44, 2432 (R = 2) 33 and 35, 3040 51 and 61. A row of up to eight tiles is
+// one step of 256 threads already.
 constexpr int64_t kWideMaxGroups = 1280;
 constexpr int kWideMinTiles = 8;
 
@@ -929,22 +947,27 @@ hipError_t launch_verify(const VerifyArgs& a, hipStream_t stream) {
   if (e != hipSuccess) return e;
   const bool want_beta = a.beta || a.exp_len;
   const bool stream_path = want_beta && !a.trajectory && a.blk.V >= 4;  // a row holds a group of four
-  int nchunk_f = nchunk;  // the finalisation's partials per position
+  const int64_t R = a.blk.R;  // the template argument of the streams below: R, or 0
+  const int rt = R <= 8 || R == 16 ? static_cast<int>(R) : 0;
+  const int nchunk_s = (a.blk.nT + stream_tiles(rt) - 1) / stream_tiles(rt);
+  const int nchunk_f = stream_path ? nchunk_s : nchunk;  // the finalisation's partials per position
   const int rows = static_cast<int>(a.blk.K) + (!a.trajectory && a.Kp == a.blk.K + 1 ? 1 : 0);
   if (stream_path && a.blk.nT > kWideMinTiles && rows * B * nchunk <= kWideMaxGroups) {
-    const dim3 grid(static_cast<unsigned>(rows * B * nchunk));
-#define DBL_WIDE(r) \
-  case r: hipLaunchKernelGGL(verify_stream_wide_kernel<r>, grid, dim3(1024), 0, stream, a, nchunk); break
-    switch (a.blk.R) {
-      DBL_WIDE(1);
-      DBL_WIDE(2);
-      DBL_WIDE(3);
-      DBL_WIDE(4);
-      DBL_WIDE(5);
-      DBL_WIDE(6);
-      DBL_WIDE(7);
-      DBL_WIDE(8);
-      default: hipLaunchKernelGGL(verify_stream_wide_kernel<0>, grid, dim3(1024), 0, stream, a, nchunk);
+    const dim3 grid(static_cast<unsigned>(rows * B * nchunk_s));
+#define DBL_WIDE(r)                                                                             \
+  hipLaunchKernelGGL(verify_stream_wide_kernel<r>, grid, dim3(kWideThreads), 0, stream, a,     \
+                     nchunk_s);                                                               \
+  break
+    switch (rt) {
+      case 1: DBL_WIDE(1);
+      case 2: DBL_WIDE(2);
+      case 3: DBL_WIDE(3);
+      case 4: DBL_WIDE(4);
+      case 5: DBL_WIDE(5);
+      case 6: DBL_WIDE(6);
+      case 7: DBL_WIDE(7);
+      case 8: DBL_WIDE(8);
+      default: DBL_WIDE(0);
     }
 #undef DBL_WIDE
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -953,17 +976,13 @@ hipError_t launch_verify(const VerifyArgs& a, hipStream_t stream) {
     // same loads. Trajectory mode keeps the beta kernel below: its stream has no residual
     // arithmetic to carry, and at R = 16 it measured 3.48 ms against 3.78 ms fused per 128-block
     // chunk.
-    const int64_t R = a.blk.R;  // the template argument of the launch below: R, or 0
-    const int rt = R <= 8 || R == 16 ? static_cast<int>(R) : 0;
-    const int nchunk_s = (a.blk.nT + stream_tiles(rt) - 1) / stream_tiles(rt);
-    nchunk_f = nchunk_s;
     const int64_t cw_many = (nchunk_s + kStreamChunksSmallR - 1) / kStreamChunksSmallR;
     const int cpw = stream_multi_chunk(rt) && rows * B * cw_many >= kStreamMinGroups
                         ? kStreamChunksSmallR : 1;
     const int64_t nwg = static_cast<int64_t>(rows) * B * ((nchunk_s + cpw - 1) / cpw);
     if (nwg > 0x7fffffff) return hipErrorInvalidConfiguration;
     const dim3 grid(static_cast<unsigned>(nwg));
-    switch (a.blk.R) {
+    switch (rt) {
       case 1: hipLaunchKernelGGL(verify_stream_kernel<1>, grid, dim3(256), 0, stream, a, nchunk_s, cpw); break;
       case 2: hipLaunchKernelGGL(verify_stream_kernel<2>, grid, dim3(256), 0, stream, a, nchunk_s, cpw); break;
       case 3: hipLaunchKernelGGL(verify_stream_kernel<3>, grid, dim3(256), 0, stream, a, nchunk_s, cpw); break;

@@ -1,6 +1,7 @@
 // Test helper (not part of the library): checks on the GPU, for every one of the 2^32 binary32
 // bit patterns, that the branch-free quantised exponential the sampler and verifier use equals the
-// determinism contract's definition quant40(detexp32(x)) = floor(detexp32(x) 2^40); and evaluates
+// determinism contract's definition quant40(detexp32(x)) = floor(detexp32(x) 2^40), and that the
+// branch-free detexp32_flat has detexp32's bits; and evaluates
 // the kernels' Philox4x32-10 (output words 0 and 1) on given counters and keys.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -20,7 +21,8 @@ __global__ __launch_bounds__(256) void quant_all_kernel(unsigned long long* bad,
     const float x = __uint_as_float(u);
     const uint64_t ref = dbl::quant40(dbl::detexp32(x));
     const uint64_t a = dbl::quant_detexp32(x);
-    if (a != ref) {
+    const bool flat = __float_as_uint(dbl::detexp32_flat(x)) == __float_as_uint(dbl::detexp32(x));
+    if (a != ref || !flat) {
       ++nbad;
       fb = fb < u ? fb : u;
     }

@@ -1,6 +1,6 @@
 """The kernels' contract primitives on the GPU (test helper tests/native/libcontract_check.so,
-built by __graft_entry__.build()): the branch-free quantised exponential against the contract's
-definition floor(detexp32(x) 2^40) for all 2^32 binary32 inputs, and Philox4x32-10's output
+built by __graft_entry__.build()): the branch-free exponentials against the contract's detexp32 and
+floor(detexp32(x) 2^40) for all 2^32 binary32 inputs, and Philox4x32-10's output
 words 0 and 1 against the published known-answer vectors and the oracle."""
 import ctypes
 import os

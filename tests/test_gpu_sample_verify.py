@@ -267,3 +267,30 @@ STREAM_EDGES = [
 @pytest.mark.parametrize("case", STREAM_EDGES, ids=[c[0] for c in STREAM_EDGES])
 def test_stream_edges(case):
     test_sample_verify_parity(case)
+
+
+# A block's draw and verification depend neither on the other blocks of the call nor on its place among
+# them, given its sequence index: the last block of a grid past the wide kernel's limit, alone and with
+# a few others. One and several chunks of 32 (R <= 4) and 40 tiles, whole and ragged rows.
+@pytest.mark.parametrize("R", [1, 3, 4, 5, 8, 9, 16])
+@pytest.mark.parametrize("V", [1155, 5002, 10368])
+def test_blocks_do_not_depend_on_the_batch(R, V):
+    from paper_2608_05448_amd import dblast as D
+    K, nT = 4, -(-V // 128)
+    B = 1300 // ((K + 1) * -(-nT // 32)) + 1
+    g = torch.Generator(device="cuda").manual_seed(R * V)
+    tls = torch.randn((B, K, R, V), generator=g, device="cuda") - 4.0
+    lmass = torch.randn((B, K, R, nT), generator=g, device="cuda")
+    lse = torch.logsumexp(lmass, -1)
+    ell = torch.randn((B, R), generator=g, device="cuda")
+    logp = torch.log_softmax(torch.randn((B, K + 1, V), generator=g, device="cuda"), -1)
+    z, x = D.dbl_sample_block(tls, lmass, lse, ell, seed=3)
+    whole = D.dbl_verify_block(tls, lmass, lse, ell, x, logp, seed=3)
+    for n in (1, 5):
+        print(f"[verify] R={R} V={V}: {n} of {B} blocks", flush=True)
+        a = [t[B - n:].clone() for t in (tls, lmass, lse, ell)]
+        z1, x1 = D.dbl_sample_block(*a, seed=3, seq_offset=B - n)
+        assert torch.equal(z1, z[B - n:]) and torch.equal(x1, x[B - n:])
+        part = D.dbl_verify_block(*a, x1, logp[B - n:].clone(), seed=3, seq_offset=B - n)
+        for key, t in part.items():
+            assert torch.equal(t, whole[key][B - n:]), (key, n)
