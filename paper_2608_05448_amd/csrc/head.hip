@@ -1429,11 +1429,24 @@ __global__ __launch_bounds__(C::kThreads, C::kWavesPerEu) void head_bf16_few_ker
 // latency at the sizes it is for, so every load that can be is in flight at once: the branch rows' chunk
 // (copied one load and one LDS write at a time, 16 in turn, that copy was most of the time: 8 rows at
 // d = 64, V = 256 7.7 -> 6.6 us) and, 32 hidden units at a time, the line of the weight row that the
-// thread alone reads (16-byte loads at any d: global loads need 4-byte alignment only). Sixteen rows per
-// workgroup where that still leaves one per CU and the walk is long enough to pay for the larger
-// reduction: the weight is then read through the caches M / 16 times (128 rows, V = 8000: 45 -> 31 us at
-// d = 256; at d = 100 the step takes 50 us with four rows, 52 with sixteen).
+// thread alone reads (16-byte loads at any d: global loads need 4-byte alignment only). With sixteen rows
+// per workgroup the weight is read through the caches M / 16 times instead of M / 4, but a row of the tile
+// that holds no branch row costs what a real one does; f32_rows16 says where it is the faster form.
 constexpr int kF32DChunk = 512;
+
+// Whether sixteen rows per workgroup are faster than four. From d = 512 on they are once three of the
+// tile's four groups of four rows are real and there is more than a workgroup per CU (us, four and sixteen
+// rows: 16 rows, d = 1024, V = 151,936 503 and 246, 4 rows 173 and 236; 64 rows, d = 512, V = 16,000 79
+// and 46; 16 rows, V = 32,768, 256 workgroups, 38 and 42). Below, the walk is too short for the larger reduction unless the tiles
+// are full or many (d = 256, V = 151,936: 16 rows 97 and 85, 20 rows 116 and 134, 128 rows 664 and 506), or,
+// where 32 does not divide d, with its walk of single units at the end, unless there are four workgroups
+// per CU (d = 300: 48 rows, V = 32,768 46 and 62; 32 rows, V = 65,536 81 and 65). At d = 160 the two are
+// within 15% of each other from 32 rows on and four rows are faster below (4 rows, V = 151,936 24 and 64).
+inline bool f32_rows16(int64_t M, int d, int64_t nT) {
+  const int64_t m16 = (M + 15) / 16, wg = nT * m16;
+  if (d >= 512) return M >= 12 && wg >= 300;
+  return d >= 256 && (M >= 64 || 16 * m16 - M < 4) && wg >= (d % 32 == 0 ? 300 : 1000);
+}
 
 template <int kF32Rows>
 __global__ __launch_bounds__(128) void head_f32_kernel(const float* __restrict__ h,
@@ -1692,7 +1705,7 @@ hipError_t launch_head(const HeadArgs& a, hipStream_t stream) {
     }
   } else {
     const int64_t m16 = (a.M + 15) / 16, m4 = (a.M + 3) / 4;
-    const bool wide = nT * m16 >= 256 && a.d >= 160;
+    const bool wide = f32_rows16(a.M, a.d, nT);
     if (m4 > 65535) return hipErrorInvalidConfiguration;
     const dim3 grid(nT, static_cast<unsigned>(wide ? m16 : m4));
     const float* h = static_cast<const float*>(a.h);

@@ -4,6 +4,7 @@ Tolerances: 2e-5 absolute on log-probabilities for fp32 inputs and 2e-3 for bf16
 fp32 accumulation (both sides read the identical bf16 values).
 """
 import math
+import time
 
 import numpy as np
 import pytest
@@ -202,3 +203,39 @@ def test_head_rows_do_not_depend_on_the_batch(d):
         part = D.dbl_head_logprobs(hd[lo:lo + n].contiguous(), wd, argmax=True)
         for a, b in zip(whole, part):
             assert torch.equal(a[lo:lo + n], b), (d, lo, n)
+
+
+def _best_us(f, n=20, rounds=5):
+    """The shortest of several runs of n calls, us per call."""
+    for _ in range(3):
+        f()
+    best = 1e9
+    for _ in range(rounds):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        for _ in range(n):
+            f()
+        torch.cuda.synchronize()
+        best = min(best, (time.perf_counter() - t0) / n * 1e6)
+    return best
+
+
+# Few rows do not pay for a tile of many: one and four rows against sixteen, which fill the 16-row tile
+# that few rows would leave mostly empty (4 rows took 0.93 of the time of 16 in it; in tiles of 4 rows
+# 0.4).
+@pytest.mark.parametrize("M,d,V", [(1, 256, 151936), (4, 256, 151936), (4, 1024, 151936)])
+def test_head_fp32_few_rows_cost_less_than_a_full_tile(M, d, V):
+    from paper_2608_05448_amd import dblast as D
+    w = torch.randn((V, d), device="cuda")
+    h = torch.randn((16, 1, 1, d), device="cuda")
+    few, full = (_best_us(lambda h=h[:m]: D.dbl_head_logprobs(h, w)) for m in (M, 16))
+    print(f"[head] fp32 {M} rows {few:.1f} us, 16 rows {full:.1f} us (d={d})", flush=True)
+    assert few < 0.85 * full
+
+
+@pytest.mark.parametrize("M,d,V", [(12, 512, 38400), (11, 512, 38400), (61, 256, 9600),
+                                   (64, 300, 32001), (128, 288, 4800)])
+def test_head_fp32_tile_rule(M, d, V):
+    h = synth.make_uniform_logits((M, 1, 1, d), 63).to(torch.float32)
+    w = (synth.make_uniform_logits((V, d), 64) / math.sqrt(d)).to(torch.float32)
+    _check(h, w, 2e-5, "fp32-tile-rule")
