@@ -256,3 +256,42 @@ def test_chain_segments(K, R):
         np.testing.assert_array_equal(out[key].cpu().numpy(), ref[want])
     for key, want in (("accept_mass", "beta"), ("al_expected", "al"), ("exp_len", "E")):
         np.testing.assert_allclose(out[key].cpu().numpy(), ref[want], rtol=1e-5, atol=1e-12)
+
+
+def test_chain_cost_grows_with_the_categories_that_count():
+    """A wavefront per position visits only the categories consistent with the drafted prefix: twice the
+    categories cost less than twice the time (2.8 times with a shuffle per category). GPU time of graph
+    replays, so that the host's share does not count."""
+    from paper_2608_05448_amd import dblast as D
+    B, K, V = 4, 16, 5000
+    g = torch.Generator(device="cuda").manual_seed(5)
+    logp = torch.log_softmax(torch.randn((B, K, V), generator=g, device="cuda"), -1)
+    us = {}
+    for R in (32, 64):
+        x_hat = torch.randint(0, V, (B, K, R), generator=g, device="cuda", dtype=torch.int32)
+        ell = torch.randn((B, R), generator=g, device="cuda")
+        x = x_hat[:, :, 0].contiguous()
+        out = dict(beta=torch.empty((B, K), device="cuda"), exp_len=torch.empty(B, device="cuda"),
+                   ws=torch.empty(D.dbl_workspace_bytes(D.DBL_OP_EXPECTED_LEN_GREEDY, B, K, R, 0, V),
+                                  dtype=torch.uint8, device="cuda"))
+        call = lambda: D.dbl_expected_len_greedy(x_hat, ell, x, logp, **out)
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            call()
+        torch.cuda.current_stream().wait_stream(side)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(20):
+                call()
+        times = []
+        for _ in range(7):
+            t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            t0.record()
+            graph.replay()
+            t1.record()
+            torch.cuda.synchronize()
+            times.append(t0.elapsed_time(t1) * 50.0)
+        us[R] = min(times)
+    print(f"[greedy] expected length, us by categories: {us}", flush=True)
+    assert us[64] < 2.2 * us[32]
