@@ -1162,15 +1162,30 @@ __device__ __forceinline__ uint32_t least_key(F ok) {
 // shares' bounds and the least of their j-th largest (j tokens of every share reach that one, so
 // the row's k-th largest does): two or three times k of them, selects among them and finishes.
 // 16 rows of 151,936 at k = 50: 11.5 + 7.1 us, against 23 + 54 us with 4 shares per row, bounds per
-// wavefront and a merge that bisected 1,600 candidates; 272 rows at k = 20 84 us (112). A list
-// that overflows, or no share with a bound, sends the row to the general path.
+// wavefront and a merge that bisected 1,600 candidates; 272 rows at k = 20 84 us (112).
 // 16 shares per row up to k = 128, 8 above: k tokens per share and the overshoot stay within a
-// share's list, and the smallest row (kSplitMinV) still has more non-empty threads than k.
+// share's list, and the smallest row (kSplitMinV) still has more non-empty threads than k. Where the
+// logits fall with the id a thread holds several of the largest and its neighbours the next, so up to 4 k
+// tokens reach the bound, or, in a flat tail, as many as share its 18 bits: a list that overflows is left
+// out if its share's largest key is below the row's bound, and otherwise its share is read again by the
+// merge workgroup, against the row's bound (16 rows, k = 128, falling by 1.1 log(id) with noise 0.7: 27 us,
+// where the general path took 467; without noise 30 us). Rows with fewer than k ids above -inf, or with
+// more than kCandCap tokens at the row's bound, take the general path.
 constexpr int kTopThreads = 512;
 constexpr int kTopEntries = kFilterRowBytes / 8;  // over all shares of a row, two heads each included
 __host__ __device__ constexpr int top_shares(int64_t k) { return k <= 128 ? 16 : 8; }
 static_assert(kSplitMinV / 4 / top_shares(128) >= 128 && kSplitMinV / 4 / top_shares(256) >= 256,
               "at least k non-empty threads per share");
+
+struct ShareGroups {  // groups of four ids g0 <= g < g1, those below gfull within V
+  int64_t g0, g1, gfull;
+};
+__device__ __forceinline__ ShareGroups share_groups(int64_t V, int shares, int share) {
+  const int64_t groups = (V + 3) / 4;
+  const int64_t per = (groups + shares - 1) / shares;
+  const int64_t g0 = min(groups, share * per), g1 = min(groups, g0 + per);
+  return {g0, g1, min(g1, V / 4)};
+}
 
 __global__ __launch_bounds__(kTopThreads) void filter_topk_share_kernel(FilterArgs a, int shares) {
   __shared__ int s_bin[3][kTopThreads];
@@ -1187,11 +1202,8 @@ __global__ __launch_bounds__(kTopThreads) void filter_topk_share_kernel(FilterAr
   const int cap = kTopEntries / shares - 2;
   const float* in = a.logits + row * V;
   float* out = a.logp + row * V;
-  // This share's groups of four: [g0, g1); thread t has g0 + t, g0 + t + 512, ...
-  const int64_t groups = (V + 3) / 4;
-  const int64_t per = (groups + shares - 1) / shares;
-  const int64_t g0 = min(groups, share * per), g1 = min(groups, g0 + per);
-  const int64_t gfull = min(g1, V / 4);  // groups of four within V
+  // This share's groups of four; thread t has g0 + t, g0 + t + 512, ...
+  const auto [g0, g1, gfull] = share_groups(V, shares, share);
   uint32_t top = 0;
   auto see = [&](float x) { top = max(top, order_key(x)); };
   const f32x4u ninf = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
@@ -1291,9 +1303,22 @@ __global__ __launch_bounds__(kTopThreads) void filter_topk_share_kernel(FilterAr
       for (int64_t v = 4 * i; v < V; ++v) take(v, in[v]);
   }
   __syncthreads();
+  // The share's largest key, by which the merge tells whether it needs a list that overflowed.
+  uint32_t most = 0;
+  if (sh_n > cap) {  // workgroup-uniform
+    most = top;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) most = max(most, static_cast<uint32_t>(__shfl_xor(most, o)));
+    if (lane_id() == 0) s_wave[0][tid >> 6] = static_cast<int>(most);
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kTopThreads / 64; ++w)
+      most = max(most, static_cast<uint32_t>(s_wave[0][w]));
+  }
   if (tid == 0) {
     list[0] = (static_cast<uint64_t>(s_low) << 32) | static_cast<uint32_t>(sh_n);
-    list[1] = jth > kKeyNegInf ? order_key(__fdiv_rn(key_value(jth), T)) : 0;
+    list[1] = (static_cast<uint64_t>(order_key(__fdiv_rn(key_value(most), T))) << 32) |
+              (jth > kKeyNegInf ? order_key(__fdiv_rn(key_value(jth), T)) : 0);
   }
 }
 
@@ -1320,32 +1345,65 @@ __global__ __launch_bounds__(kFT, 8) void filter_topk_merge_kernel(FilterArgs a,
 #pragma unroll
   for (int i = 0; i < kTopEntries / kFT; ++i) e[i] = lists[tid + i * kFT];
   const uint64_t head = lists[(lane_id() % shares) * per];
+  const uint64_t ends = lists[(lane_id() % shares) * per + 1];
   uint32_t kth = static_cast<uint32_t>(head >> 32);
-  uint32_t jth = static_cast<uint32_t>(lists[(lane_id() % shares) * per + 1]);
-  const bool over = __ballot(static_cast<int>(static_cast<uint32_t>(head)) > per - 2) != 0;
+  uint32_t jth = static_cast<uint32_t>(ends);
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) {
     kth = max(kth, static_cast<uint32_t>(__shfl_xor(kth, o)));
     jth = min(jth, static_cast<uint32_t>(__shfl_xor(jth, o)));
   }
   const uint32_t least = max(kth, jth);
-  if (over || least == 0) {
+  // Shares whose list overflowed (logits that fall with the id, or coarse ones) and that hold a token
+  // that counts: their ids are read again, against the row's bound.
+  const uint64_t over = __ballot(lane_id() < shares &&
+                                 static_cast<int>(static_cast<uint32_t>(head)) > per - 2 &&
+                                 static_cast<uint32_t>(ends >> 32) >= least);
+  if (tid == 0) sh_n = 0;
+  __syncthreads();
+  auto keep = [&](uint64_t c) {
+    const int slot = atomicAdd(&sh_n, 1);
+    if (slot < kCandCap) cand[slot] = c;
+  };
+#pragma unroll
+  for (int i = 0; i < kTopEntries / kFT; ++i) {
+    const int at = tid + i * kFT, share = at / per, slot = at % per;
+    const int cnt = static_cast<int>(static_cast<uint32_t>(__shfl(head, share)));
+    if (slot > 1 && slot < 2 + cnt && !(over >> share & 1) &&
+        static_cast<uint32_t>(e[i] >> 32) >= least)
+      keep(e[i]);
+  }
+  if (over && least) {
+    const float T = a.temperature;
+    const uint32_t x_low =
+        least_key([&](uint32_t q) { return order_key(__fdiv_rn(key_value(q), T)) >= least; });
+    auto take = [&](int64_t v, float x) {
+      if (order_key(x) >= x_low) keep(visit_key(order_key(__fdiv_rn(x, T)), v));
+    };
+    for (uint64_t left = over; left; left &= left - 1) {
+      const auto [g0, g1, gfull] =
+          share_groups(V, shares, __ffsll(static_cast<unsigned long long>(left)) - 1);
+      int64_t i = g0 + tid;
+#pragma unroll 4
+      for (; i < gfull; i += kFT) {
+        const f32x4u x = *reinterpret_cast<const f32x4u*>(in + 4 * i);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) take(4 * i + q, x[q]);
+      }
+      if (i < g1)
+        for (int64_t v = 4 * i; v < V; ++v) take(v, in[v]);
+    }
+  }
+  __syncthreads();
+  const int n = sh_n;
+  // Without a bound (too few threads of every share hold a logit above -inf) the lists hold all of
+  // those logits, if none overflowed.
+  if (n > kCandCap || n < a.top_k || (over && !least)) {
     const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(in) & 15) == 0 &&
                      (reinterpret_cast<uintptr_t>(out) & 15) == 0;
     filter_general(a, in, out, vec, hist, red, redd, &sh_digit, &sh_above);
     return;
   }
-  if (tid == 0) sh_n = 0;
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < kTopEntries / kFT; ++i) {
-    const int at = tid + i * kFT, share = at / per, slot = at % per;
-    const int cnt = static_cast<int>(static_cast<uint32_t>(__shfl(head, share)));
-    if (slot > 1 && slot < 2 + cnt && static_cast<uint32_t>(e[i] >> 32) >= least)
-      cand[atomicAdd(&sh_n, 1)] = e[i];
-  }
-  __syncthreads();
-  const int n = sh_n;
   block_sort_desc(cand, n);
   // the tokens at or above the k-th largest s: at most 64 of them finish in wavefront 0
   const uint32_t tk = static_cast<uint32_t>(cand[a.top_k - 1] >> 32);

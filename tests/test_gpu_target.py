@@ -32,6 +32,13 @@ def _logits(N, V, seed, ties=False):
         # computes the masses in every pass, not the bins alone)
         g = (-27.5 + 0.15 * synth.make_uniform_logits((N, V), seed).numpy()).astype(np.float32)
         g[:, 0] = 0.0
+    elif ties in ("falling", "falling-noise"):   # logits that fall with the id, as in a vocabulary
+        # ordered by frequency; without noise neighbours in the tail differ by 1e-5
+        g = -1.1 * np.log1p(np.arange(V))[None, :] + np.zeros((N, 1))
+        if ties == "falling-noise":
+            g = g + 0.7 * np.random.default_rng(seed).standard_normal((N, V))
+    elif ties == "bf16":   # logits of a bf16 head
+        g = torch.from_numpy(g).to(torch.bfloat16).float().numpy()
     elif ties == "masked":   # the last quarter of the vocabulary is never allowed
         g = g.astype(np.float32)
         g[:, V - V // 4:] = -np.inf
@@ -168,3 +175,48 @@ def test_target_scale_normalises():
             # binary32 results (half a unit of the value) of a normaliser good to 2^-32
             err = (out.cpu().double() - want).abs()
             assert (err <= want.abs() * 2.0 ** -23 + 2.0 ** -30).all(), (V, T, err.max())
+
+
+# Top-k rows whose shares list more tokens than they have room for: the smallest and ragged vocabularies
+# (shares of 1024 ids, a last partial group of four) and the full one, both share counts, with lists that
+# count (the first shares' or, with noise, most of them) and lists that do not (the tail's).
+FALLING = [(f"{t}-{V}-k{k}", 3, V, T, k, p, t)
+           for t in ("falling", "falling-noise", "bf16")
+           for V, T, k, p in ((151936, 0.7, 5, 0.95), (151936, 1.0, 100, 1.0), (151936, 0.7, 128, 0.95),
+                              (151935, 1.3, 256, 1.0), (40001, 0.7, 128, 0.9), (16384, 1.0, 128, 1.0),
+                              (16387, 1.0, 256, 0.95))]
+
+
+@pytest.mark.parametrize("case", FALLING, ids=[c[0] for c in FALLING])
+def test_target_falling_logits(case):
+    test_target_filter_parity(case)
+
+
+def _best_us(f, n=10, rounds=5):
+    """The shortest of several runs of n calls, us per call."""
+    for _ in range(3):
+        f()
+    best = 1e9
+    for _ in range(rounds):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        for _ in range(n):
+            f()
+        torch.cuda.synchronize()
+        best = min(best, (time.perf_counter() - t0) / n * 1e6)
+    return best
+
+
+def test_target_topk_time_in_any_order():
+    """Top-k rows whose logits fall with the id take about as long as the same logits shuffled (24 times
+    as long when a share's overflowing list sent the row to the general path)."""
+    from paper_2608_05448_amd import dblast as D
+    N, V = 16, 151936
+    fall = torch.from_numpy(_logits(N, V, 3, "falling-noise")).cuda()
+    mono = torch.from_numpy(_logits(N, V, 3, "falling")).cuda()
+    mixed = fall[:, torch.randperm(V, device="cuda")].contiguous()
+    for k in (20, 128, 256):
+        us = [_best_us(lambda x=x: D.dbl_target_logprobs(x, 0.7, k, 0.95)) for x in (mixed, fall, mono)]
+        print(f"[target] k={k}: shuffled {us[0]:.1f} us, falling {us[1]:.1f}, without noise {us[2]:.1f}",
+              flush=True)
+        assert max(us[1:]) < 4 * us[0]
