@@ -549,22 +549,24 @@ __device__ bool filter_fast(const FilterArgs& a, const float* in, float* out, bo
 }
 
 // General path: exact radix selections over the keys of s (every k, and the nucleus alone),
-// reading the row several times and writing all of it.
+// reading the row several times and writing all of it. MAX: m_known is the row's largest s.
+template <bool MAX = false>
 __device__ void filter_general(const FilterArgs& a, const float* in, float* out, bool vec,
                                uint64_t* hist, uint64_t* red, double* redd, uint32_t* sh_digit,
-                               uint64_t* sh_above) {
+                               uint64_t* sh_above, float m_known = 0.0f) {
   const int tid = threadIdx.x;
   const int64_t V = a.V;
   const float T = a.temperature;
   auto s_of = [&](int64_t v) { return __fdiv_rn(in[v], T); };
-  // Row maximum (key of the largest s).
-  uint32_t mk = 0;
-  row_scan<4>(in, V, T, vec, [&](int64_t, float sv) {
-    const uint32_t k = order_key(sv);
-    mk = k > mk ? k : mk;
-  });
-  const uint32_t max_key = static_cast<uint32_t>(block_max_u64(mk, red));
-  const float m = __uint_as_float((max_key & 0x80000000u) ? (max_key & 0x7FFFFFFFu) : ~max_key);
+  float m = m_known;
+  if constexpr (!MAX) {  // row maximum (key of the largest s)
+    uint32_t mk = 0;
+    row_scan<4>(in, V, T, vec, [&](int64_t, float sv) {
+      const uint32_t k = order_key(sv);
+      mk = k > mk ? k : mk;
+    });
+    m = key_value(static_cast<uint32_t>(block_max_u64(mk, red)));
+  }
 
   // Top-k: the k-th largest key, by count.
   uint32_t tk = 0;  // keep keys >= tk
@@ -1426,40 +1428,44 @@ __global__ __launch_bounds__(kFT, 8) void filter_topk_merge_kernel(FilterArgs a,
 //               non-increasing in the logit, so a bin is an interval of logits);
 //   4. gather   the crossing bin's tokens appended to the row's list: the row is read again with two
 //               compares per id;
-//   5. cut      one workgroup per row: the list's order, the cut and the normaliser;
+//   5. cut      one workgroup per row: the list's order, the cut and the normaliser, or, where the
+//               bin's tokens cannot be listed, the general path from the maximum on;
 //   6. write    kept ids by comparing logit keys, so only kept ids are divided.
 // The mass pass is bound by its arithmetic (about 50 lane instructions per id for the contract's
 // division and quantised exponential), the others by the row's traffic. 272 rows of 151,936
 // logits at T = 0.7: 27 + 54 + 8 + 25 + 10 + 53 us (169 us per call, 276 with one workgroup per
 // row); 16 rows 40 us (123).
-struct NucleusRow {  // a row's workspace: this, seg_max[segs], then the list
-  uint64_t bins[kNucBins];
+struct NucleusRow {  // a row's workspace: this, then the bins and seg_max[segs], later the list
   uint64_t before, tp;
   double lse;
   float m;
   float edge[2];  // the crossing bin's logits: [edge[0], edge[1])
   int sure;       // every token of the bin has positive mass
   int count;      // tokens listed
-  int live;       // the row has mass
+  int listed;     // the row has mass, and its crossing bin may fit the list
 };
 constexpr int64_t kNucMaxSegs = (int64_t{1} << 24) / kSegElems;
 static_assert(sizeof(NucleusRow) % 8 == 0 &&
-                  sizeof(NucleusRow) + 4 * kNucMaxSegs + 8 <= kFilterRowBytes,
+                  sizeof(NucleusRow) + 8 * kNucBins + 4 * kNucMaxSegs <= kFilterRowBytes,
               "a row's workspace");
+// Entries of the list, which takes the place of the bins and maxima once the edge is known: 4,090,
+// where the one-workgroup form's holds kCandCap.
+constexpr int kNucList = static_cast<int>((kFilterRowBytes - sizeof(NucleusRow)) / 8);
+static_assert(kNucList <= kCandCap && kNucList >= kCandCap - 8, "the list's entries");
 constexpr int kMassU = 8;
 constexpr int kMassElems = 4 * kFT * kMassU;
 
 __device__ __forceinline__ NucleusRow* nucleus_row(const FilterArgs& a, int64_t row) {
   return reinterpret_cast<NucleusRow*>(a.row_ws + row * kFilterRowBytes);
 }
+__device__ __forceinline__ uint64_t* nucleus_bins(NucleusRow* w) {
+  return reinterpret_cast<uint64_t*>(w + 1);
+}
 __device__ __forceinline__ uint32_t* nucleus_seg_max(NucleusRow* w) {
-  return reinterpret_cast<uint32_t*>(w + 1);
+  return reinterpret_cast<uint32_t*>(nucleus_bins(w) + kNucBins);
 }
-__device__ __forceinline__ uint64_t* nucleus_list(NucleusRow* w, int segs) {
-  return reinterpret_cast<uint64_t*>(w + 1) + (segs + 1) / 2;
-}
-__device__ __forceinline__ int nucleus_cap(int segs) {  // entries of the list, about 2,030
-  return min(kCandCap, static_cast<int>((kFilterRowBytes - sizeof(NucleusRow)) / 8) - (segs + 1) / 2);
+__device__ __forceinline__ uint64_t* nucleus_list(NucleusRow* w) {
+  return reinterpret_cast<uint64_t*>(w + 1);
 }
 
 // s of the row's largest logit, from the segments' keys; every wavefront computes it.
@@ -1478,7 +1484,7 @@ __global__ __launch_bounds__(kSegT) void nucleus_max_kernel(FilterArgs a, int se
   float x[kSegU][4];
   load_groups<kSegT, kSegU>(a.logits + row * a.V, a.V, seg * kSegElems, threadIdx.x, x);
   if (seg == 0)
-    for (int i = threadIdx.x; i < kNucBins; i += kSegT) w->bins[i] = 0;
+    for (int i = threadIdx.x; i < kNucBins; i += kSegT) nucleus_bins(w)[i] = 0;
   uint32_t k = 0;
 #pragma unroll
   for (int i = 0; i < kSegU; ++i)
@@ -1523,7 +1529,7 @@ __global__ __launch_bounds__(kFT) void nucleus_mass_kernel(FilterArgs a, int par
     all([&](float v) { return __fdiv_rn(v, T); });
   __syncthreads();
   for (int i = threadIdx.x; i < kNucBins; i += kFT)
-    if (bins[i]) atomicAdd(reinterpret_cast<unsigned long long*>(&w->bins[i]),
+    if (bins[i]) atomicAdd(reinterpret_cast<unsigned long long*>(&nucleus_bins(w)[i]),
                            static_cast<unsigned long long>(bins[i]));
 }
 
@@ -1533,7 +1539,7 @@ __global__ __launch_bounds__(kFT) void nucleus_edge_kernel(FilterArgs a, int seg
   const int tid = threadIdx.x;
   const float T = a.temperature;
   NucleusRow* w = nucleus_row(a, row);
-  const uint64_t m0 = w->bins[2 * tid], m1 = w->bins[2 * tid + 1];
+  const uint64_t m0 = nucleus_bins(w)[2 * tid], m1 = nucleus_bins(w)[2 * tid + 1];
   const float m = nucleus_max(w, segs, T);
   int bstar;
   uint64_t before, tp;
@@ -1552,7 +1558,11 @@ __global__ __launch_bounds__(kFT) void nucleus_edge_kernel(FilterArgs a, int seg
     w->m = m;
     w->sure = bstar <= kNucSureBin;
     w->count = 0;
-    w->live = live;
+    // No token of bin b has more mass than 2^40 e^(-b / kNucScale): a crossing bin that must hold more
+    // tokens than the one-workgroup form lists is not gathered either.
+    const double most = 0x1p40 * exp(-static_cast<double>(bstar) / static_cast<double>(kNucScale));
+    w->listed = live && static_cast<double>(nucleus_bins(w)[live ? bstar : 0]) <=
+                            1.001 * (kCandCap + 1) * most;
   }
 }
 
@@ -1562,30 +1572,44 @@ __global__ __launch_bounds__(kSegT) void nucleus_gather_kernel(FilterArgs a, int
   NucleusRow* w = nucleus_row(a, row);
   float x[kSegU][4];
   load_groups<kSegT, kSegU>(in, a.V, seg * kSegElems, threadIdx.x, x);
-  if (!w->live) return;
-  const float lo = w->edge[0], hi = w->edge[1];
+  if (!w->listed) return;
+  __shared__ int s_n, s_base;
+  const float lo = w->edge[0], hi = w->edge[1], m = w->m;
+  const bool sure = w->sure;
   uint32_t hit = 0;
 #pragma unroll
   for (int i = 0; i < kSegU; ++i)
 #pragma unroll
     for (int q = 0; q < 4; ++q) hit |= x[i][q] >= lo && x[i][q] < hi ? 1u << (4 * i + q) : 0;
-  uint64_t* list = nucleus_list(w, segs);
-  const int cap = nucleus_cap(segs);
-  while (hit) {  // few: read again rather than picked out of the registers
-    const int at = __ffs(static_cast<int>(hit)) - 1;
-    hit &= hit - 1;
-    const int64_t v = seg * kSegElems + 4 * (static_cast<int>(threadIdx.x) + (at >> 2) * kSegT) + (at & 3);
-    if (v >= a.V) continue;  // a masked place of the last segment
-    const float sv = __fdiv_rn(in[v], a.temperature);
-    if (w->sure || quant_detexp32(__fsub_rn(sv, w->m))) {
-      const int slot = atomicAdd(&w->count, 1);
-      if (slot < cap) list[slot] = visit_key(order_key(sv), v);
-    }
+  // Few, as a rule: read again rather than picked out of the registers.
+  auto id_of = [&](int at) {
+    return seg * kSegElems + 4 * (static_cast<int>(threadIdx.x) + (at >> 2) * kSegT) + (at & 3);
+  };
+  auto s_of = [&](int64_t v) { return __fdiv_rn(in[v], a.temperature); };
+  for (uint32_t left = hit; left; left &= left - 1) {
+    const int at = __ffs(static_cast<int>(left)) - 1;
+    const int64_t v = id_of(at);  // past V: a masked place of the last segment
+    if (v >= a.V || !(sure || quant_detexp32(__fsub_rn(s_of(v), m)))) hit &= ~(1u << at);
+  }
+  // One addition to the row's counter per workgroup: with one per token, rows whose bin holds
+  // thousands wait for each other's.
+  if (threadIdx.x == 0) s_n = 0;
+  __syncthreads();
+  int slot = hit ? atomicAdd(&s_n, __popc(hit)) : 0;
+  __syncthreads();
+  if (s_n == 0) return;  // workgroup-uniform
+  if (threadIdx.x == 0) s_base = atomicAdd(&w->count, s_n);
+  __syncthreads();
+  slot += s_base;
+  uint64_t* list = nucleus_list(w);
+  for (; hit; hit &= hit - 1, ++slot) {
+    const int64_t v = id_of(__ffs(static_cast<int>(hit)) - 1);
+    if (slot < kNucList) list[slot] = visit_key(order_key(s_of(v)), v);
   }
 }
 
 // Eight waves per SIMD, so that two rows share a CU (272 rows: 13.1 -> 10.3 us); only the fallback spills.
-__global__ __launch_bounds__(kFT, 8) void nucleus_cut_kernel(FilterArgs a, int segs) {
+__global__ __launch_bounds__(kFT, 8) void nucleus_cut_kernel(FilterArgs a) {
   __shared__ uint64_t hist[256];
   __shared__ uint64_t nbins[kNucBins];
   __shared__ uint64_t cand[kCandCap];
@@ -1600,16 +1624,16 @@ __global__ __launch_bounds__(kFT, 8) void nucleus_cut_kernel(FilterArgs a, int s
   const float T = a.temperature;
   const int tid = threadIdx.x;
   NucleusRow* w = nucleus_row(a, row);
-  const uint64_t* list = nucleus_list(w, segs);
+  const uint64_t* list = nucleus_list(w);
   const int n = w->count;
   const float m = w->m;
-  if (!w->live || n > nucleus_cap(segs)) {  // the list overflowed, or a row without mass
+  if (!w->listed || n > kNucList) {  // a row without mass, or a bin that does not fit
     const float* in = a.logits + row * V;
     float* out = a.logp + row * V;
     const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(in) & 15) == 0 &&
                      (reinterpret_cast<uintptr_t>(out) & 15) == 0;
-    if (!w->live || !filter_nucleus(a, in, out, vec, nbins, cand, red, &sh_n))
-      filter_general(a, in, out, vec, hist, red, redd, &sh_digit, &sh_above);
+    if (!w->listed || n > kCandCap || !filter_nucleus(a, in, out, vec, nbins, cand, red, &sh_n))
+      filter_general<true>(a, in, out, vec, hist, red, redd, &sh_digit, &sh_above, m);
     if (tid == 0) a.cuts[row] = FilterCut{0, 0, 0, 1};
     return;
   }
@@ -1748,7 +1772,7 @@ hipError_t launch_filter(const FilterArgs& a, hipStream_t stream) {
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(nucleus_gather_kernel, grid(segs), dim3(kSegT), 0, stream, a, segs);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(nucleus_cut_kernel, rows, dim3(kFT), 0, stream, a, segs);
+    hipLaunchKernelGGL(nucleus_cut_kernel, rows, dim3(kFT), 0, stream, a);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(nucleus_write_kernel, grid(segs), dim3(kSegT), 0, stream, a, segs);
   } else if (split && k_off && !nucleus) {

@@ -220,3 +220,40 @@ def test_target_topk_time_in_any_order():
         print(f"[target] k={k}: shuffled {us[0]:.1f} us, falling {us[1]:.1f}, without noise {us[2]:.1f}",
               flush=True)
         assert max(us[1:]) < 4 * us[0]
+
+
+# Nucleus rows by the number of tokens in the crossing bin: the former list's room and the present one's
+# (4,090), the one-workgroup form's 4,096, and more, up to bins that are known from their mass not to fit.
+@pytest.mark.parametrize("T", [1.0, 0.7])
+@pytest.mark.parametrize("n", [1, 2030, 2100, 4089, 4090, 4091, 4096, 4097, 4200, 30000])
+def test_target_crowded_nucleus_bin(n, T):
+    from paper_2608_05448_amd import dblast as D
+    N, V = 2, 40003
+    rng = np.random.default_rng(n)
+    s = np.full((N, V), -60.0)
+    for r in range(N):
+        ids = rng.permutation(V)[:n + 1]
+        s[r, ids[0]] = 0.0
+        s[r, ids[1:]] = -5.0 - 0.004 * rng.random(n)   # one bin: -5.0089 < s - m <= -4.9953
+    lg = (s * T).astype(np.float32)
+    p = float(np.float32((1.0 + 0.5 * n * np.exp(-5.002)) / (1.0 + n * np.exp(-5.002))))
+    lgd = torch.from_numpy(lg).cuda()
+    got = D.dbl_target_logprobs(lgd, T, 0, p)
+    assert torch.equal(got, D.dbl_target_logprobs(lgd, T, 0, p, split=False))
+    got, want = got.cpu().numpy(), TG.filter_logprobs(lg, T, 0, p)
+    fin = np.isfinite(want)
+    print(f"[target] n={n} T={T}: kept per row {fin.sum(1).tolist()}", flush=True)
+    assert np.array_equal(np.isfinite(got), fin)
+    assert np.max(np.abs(got[fin] - want[fin])) < 2e-6
+
+
+@pytest.mark.parametrize("scale,most", [(1.0, 0.8), (0.01, 1.1)])
+def test_target_wide_nucleus_is_no_slower_split(scale, most):
+    """Rows at high temperature, split against one workgroup per row: a few thousand tokens in the crossing
+    bin (1.22 times as long when their list overflowed), and nearly flat rows, which need the general
+    path (1.31 times)."""
+    from paper_2608_05448_amd import dblast as D
+    lg = scale * torch.randn((16, 151936), device="cuda")
+    a, b = (_best_us(lambda x=x: D.dbl_target_logprobs(lg, 5.0, 0, 0.9, split=x)) for x in (True, False))
+    print(f"[target] noise {scale}: split {a:.1f} us, one workgroup per row {b:.1f}", flush=True)
+    assert a < most * b
