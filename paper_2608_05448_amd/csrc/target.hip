@@ -1000,10 +1000,14 @@ __device__ __forceinline__ SegStat seg_stat(const float* in, int64_t V, int64_t 
   // a group without a segment takes part with an empty one
   load_groups<kSegT, kSegU>(in, live ? V : 0, live ? seg * kSegElems : 0, t, x);
   uint32_t mk = 0;
+  bool nan = false;  // a NaN with the sign bit set is the least key, and exp_sum takes it for 0
 #pragma unroll
   for (int i = 0; i < kSegU; ++i)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) mk = max(mk, order_key(x[i][q]));
+    for (int q = 0; q < 4; ++q) {
+      mk = max(mk, order_key(x[i][q]));
+      nan = nan || x[i][q] != x[i][q];
+    }
   const float m = __fdiv_rn(key_value(group_max_u32(mk, red, grp)), T);
   const int64_t left = live ? V - seg * kSegElems : 0;  // groups of four past V add nothing
   double s = 0.0;
@@ -1022,6 +1026,7 @@ __device__ __forceinline__ SegStat seg_stat(const float* in, int64_t V, int64_t 
     all([&](float v) { return div.quick(v); });
   else
     all([&](float v) { return __fdiv_rn(v, T); });
+  if (nan) s = NAN;  // as every sum with a NaN
   s = wave_sum_f64(s);
   if (lane_id() == 0) redd[4 * grp + ((threadIdx.x >> 6) & 3)] = s;
   __syncthreads();
@@ -1440,7 +1445,7 @@ struct NucleusRow {  // a row's workspace: this, then the bins and seg_max[segs]
   double lse;
   float m;
   float edge[2];  // the crossing bin's logits: [edge[0], edge[1])
-  int sure;       // every token of the bin has positive mass
+  int bin;        // the crossing bin; up to kNucSureBin every token of it has positive mass
   int count;      // tokens listed
   int listed;     // the row has mass, and its crossing bin may fit the list
 };
@@ -1556,7 +1561,7 @@ __global__ __launch_bounds__(kFT) void nucleus_edge_kernel(FilterArgs a, int seg
     w->before = before;
     w->tp = tp;
     w->m = m;
-    w->sure = bstar <= kNucSureBin;
+    w->bin = bstar;
     w->count = 0;
     // No token of bin b has more mass than 2^40 e^(-b / kNucScale): a crossing bin that must hold more
     // tokens than the one-workgroup form lists is not gathered either.
@@ -1575,7 +1580,7 @@ __global__ __launch_bounds__(kSegT) void nucleus_gather_kernel(FilterArgs a, int
   if (!w->listed) return;
   __shared__ int s_n, s_base;
   const float lo = w->edge[0], hi = w->edge[1], m = w->m;
-  const bool sure = w->sure;
+  const bool sure = w->bin <= kNucSureBin;
   uint32_t hit = 0;
 #pragma unroll
   for (int i = 0; i < kSegU; ++i)
@@ -1664,13 +1669,17 @@ __global__ __launch_bounds__(kSegT) void nucleus_write_kernel(FilterArgs a, int 
   if (c.done) return;
   const float m = w->m;
   const double lse = w->lse;
+  // A NaN with the sign bit set, the least key, stays NaN where filter_nucleus, which takes it for a
+  // token of bin 0, keeps it.
+  const bool keep_nan = w->bin > 0 && w->bin <= kNucSureBin;
 #pragma unroll
   for (int i = 0; i < kSegU; ++i)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const uint32_t k = order_key(x[i][q]);
       const uint32_t v = static_cast<uint32_t>(seg * kSegElems + 4 * (threadIdx.x + i * kSegT) + q);
-      const bool kept = k >= c.key_above || (k >= c.key_at && v <= c.last_id);
+      const bool kept = k >= c.key_above || (k >= c.key_at && v <= c.last_id) ||
+                        (keep_nan && x[i][q] != x[i][q]);
       float o = -INFINITY;
       if (kept) o = log_prob(__fdiv_rn(x[i][q], a.temperature), m, lse);
       x[i][q] = o;

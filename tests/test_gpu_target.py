@@ -257,3 +257,37 @@ def test_target_wide_nucleus_is_no_slower_split(scale, most):
     a, b = (_best_us(lambda x=x: D.dbl_target_logprobs(lg, 5.0, 0, 0.9, split=x)) for x in (True, False))
     print(f"[target] noise {scale}: split {a:.1f} us, one workgroup per row {b:.1f}", flush=True)
     assert a < most * b
+
+
+NAN_ROWS = [(V, T, k, p) for V, T, k, p in (
+    (5, 1.0, 0, 1.0), (3001, 0.7, 0, 1.0), (16384, 1.3, 0, 1.0), (40001, 0.7, 0, 1.0), (40001, 1.0, 0, 1.0),
+    (20000, 0.7, 0, 0.9), (40001, 0.7, 0, 0.9), (151936, 1.0, 0, 0.95), (40001, 0.7, 0, 0.01),
+    (20001, 0.7, 20, 0.9), (40001, 1.0, 200, 1.0), (3001, 1.0, 20, 0.9))]
+
+
+@pytest.mark.parametrize("V,T,k,p", NAN_ROWS)
+def test_target_nan_logits(V, T, k, p):
+    """A NaN logit of either sign shows: under the temperature alone the whole row is NaN, as in the
+    oracle; under the filters both launch forms agree, and a NaN without the sign bit, the largest key,
+    makes every kept value NaN. The call's other rows do not change."""
+    from paper_2608_05448_amd import dblast as D
+    at = sorted({0, V // 3, V // 2, V - 1})
+    lg = _logits(2 * len(at) + 1, V, 41)
+    for i, v in enumerate(at):
+        lg[2 * i, v] = np.float32("nan")
+        lg[2 * i + 1, v] = np.copysign(np.float32("nan"), np.float32(-1.0))
+    assert np.signbit(lg[1, at[0]]) and not np.signbit(lg[0, at[0]])
+    lgd = torch.from_numpy(lg).cuda()
+    got = D.dbl_target_logprobs(lgd, T, k, p).cpu().numpy()
+    one = D.dbl_target_logprobs(lgd, T, k, p, split=False).cpu().numpy()
+    assert np.array_equal(got, one, equal_nan=True)
+    want = TG.filter_logprobs(lg[-1:], T, k, p)[0]
+    fin = np.isfinite(want)
+    assert np.array_equal(np.isfinite(got[-1]), fin) and np.abs(got[-1][fin] - want[fin]).max() < 2e-6
+    for i, v in enumerate(at):
+        if k == 0 and p == 1.0:
+            assert np.isnan(got[2 * i:2 * i + 2]).all(), v
+        else:
+            assert not np.isfinite(got[2 * i]).any() and np.isnan(got[2 * i, v]), v
+            if k == 0 and p > 0.5:
+                assert np.isnan(got[2 * i + 1, v]), v
