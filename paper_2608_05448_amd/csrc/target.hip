@@ -967,24 +967,6 @@ __device__ __forceinline__ uint32_t group_max_u32(uint32_t v, uint32_t* red, int
   return m;
 }
 
-// e^x for x <= 0 to 2^-32 relative: Cody-Waite reduction and the Taylor polynomial of degree 8 in
-// binary64 (0.3466^9 / 9! < 2^-32), for sums whose result is rounded to binary32. 0 for -inf, NaN
-// and below -708.
-__device__ __forceinline__ double exp_sum(double x) {
-  const double n = rint(x * 0x1.71547652b82fep+0);
-  const double r = fma(n, -0x1.62e42fefa39efp-1, x);
-  double p = 1.0 / 40320.0;
-  p = fma(p, r, 1.0 / 5040.0);
-  p = fma(p, r, 1.0 / 720.0);
-  p = fma(p, r, 1.0 / 120.0);
-  p = fma(p, r, 1.0 / 24.0);
-  p = fma(p, r, 1.0 / 6.0);
-  p = fma(p, r, 0.5);
-  p = fma(p, r, 1.0);
-  p = fma(p, r, 1.0);
-  return x > -708.0 ? ldexp(p, static_cast<int>(n)) : 0.0;
-}
-
 // Maximum m of s and sum of exp(s - m) of one segment, by a group of 256 threads (group grp of
 // the workgroup; every thread calls it): the same order of operations whichever kernel runs it.
 struct SegStat {
@@ -1000,33 +982,20 @@ __device__ __forceinline__ SegStat seg_stat(const float* in, int64_t V, int64_t 
   // a group without a segment takes part with an empty one
   load_groups<kSegT, kSegU>(in, live ? V : 0, live ? seg * kSegElems : 0, t, x);
   uint32_t mk = 0;
-  bool nan = false;  // a NaN with the sign bit set is the least key, and exp_sum takes it for 0
 #pragma unroll
   for (int i = 0; i < kSegU; ++i)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      mk = max(mk, order_key(x[i][q]));
-      nan = nan || x[i][q] != x[i][q];
-    }
+    for (int q = 0; q < 4; ++q) mk = max(mk, order_key(x[i][q]));
   const float m = __fdiv_rn(key_value(group_max_u32(mk, red, grp)), T);
+  // A segment of -inf alone has the sum 0; a NaN anywhere makes it NaN.
+  const double md = m == -INFINITY ? 0.0 : static_cast<double>(m);
   const int64_t left = live ? V - seg * kSegElems : 0;  // groups of four past V add nothing
   double s = 0.0;
-  auto all = [&](auto scale) {
 #pragma unroll
-    for (int i = 0; i < kSegU; ++i)
-      if (4 * kSegT * i < left)
+  for (int i = 0; i < kSegU; ++i)
+    if (4 * kSegT * i < left)
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          s += exp_sum(static_cast<double>(scale(x[i][q])) - static_cast<double>(m));
-  };
-  // Quotient's short form where no logit that counts is out of its range: a dividend below 2^-100
-  // changes its term by less than 2^-80 of it, an infinite one has term 0 as its NaN has here.
-  const Quotient div(T);
-  if (div.short_form && fabsf(m) < 0x1p80f)
-    all([&](float v) { return div.quick(v); });
-  else
-    all([&](float v) { return __fdiv_rn(v, T); });
-  if (nan) s = NAN;  // as every sum with a NaN
+      for (int q = 0; q < 4; ++q) s += exp(static_cast<double>(__fdiv_rn(x[i][q], T)) - md);
   s = wave_sum_f64(s);
   if (lane_id() == 0) redd[4 * grp + ((threadIdx.x >> 6) & 3)] = s;
   __syncthreads();
@@ -1060,8 +1029,9 @@ __device__ __forceinline__ float log_prob(float sv, float m, double lse) {
 }
 
 // Temperature alone, split: statistics per segment, then the output. Two reads and one write of
-// the row, bound by that traffic and the exponentials: 272 rows of 151,936 logits 96 us, 16 rows
-// 14 us, where one workgroup per row with three reads took 251 and 115.
+// the row, bound by that traffic and the binary64 exponentials: 272 rows of 151,936 logits 110 us, 16
+// rows 16 us, where one workgroup per row with three reads took 251 and 115 (a polynomial good to 2^-32
+// in place of the exponential: 97 and 14 us).
 __global__ __launch_bounds__(kSegT) void filter_stats_kernel(FilterArgs a, int segs) {
   __shared__ uint32_t red[4];
   __shared__ double redd[4];
@@ -1086,8 +1056,8 @@ __global__ __launch_bounds__(kSegT) void filter_scale_kernel(FilterArgs a, int s
 }
 
 // Temperature alone, rows of up to two segments: one 256-thread workgroup per row with the same
-// arithmetic, eight to a CU (1000 rows of 3000 ids: 13 us, against 34 with the 1024-thread form
-// below, of which a CU holds one; at 16,384 ids 300 rows take 18 us and one row 12, split 17 and 14).
+// arithmetic, five to a CU (1000 rows of 3000 ids: 14 us, against 34 with the 1024-thread form
+// below, of which a CU holds one; at 16,384 ids 300 rows take 22 us, split, at one id more, 21).
 constexpr int kRowSegs = 2;
 __global__ __launch_bounds__(kSegT) void filter_scale_rows_kernel(FilterArgs a, int segs) {
   __shared__ uint32_t red[4];
