@@ -132,13 +132,16 @@ def ntiles(V: int) -> int:
     return (V + VTILE - 1) // VTILE
 
 
-@functools.lru_cache(maxsize=1024)
 def dbl_workspace_bytes(op: int, B: int, K: int, R: int, d: int, V: int) -> int:
     return int(load().dbl_workspace_bytes(op, Shape(B, K, R, d, V)))
 
 
+# Looked up by a shape's own fields, which are plain integers, never by a caller's objects.
+_workspace_bytes = functools.lru_cache(maxsize=1024)(dbl_workspace_bytes)
+
+
 def _workspace(op, shape, device, ws=None):
-    n = dbl_workspace_bytes(op, shape.B, shape.K, shape.R, shape.d, shape.V)
+    n = _workspace_bytes(op, shape.B, shape.K, shape.R, shape.d, shape.V)
     if n == 0:
         return None, 0
     if ws is not None:

@@ -67,6 +67,19 @@ def test_workspace_sizes(lib):
     assert lib.dbl_workspace_bytes(D.DBL_OP_SAMPLE, S(0, 4, 2, 8, 256)) == 0
 
 
+def test_workspace_size_takes_its_arguments_as_they_are(lib):
+    """Nothing is looked up by the caller's objects: a size that is refused is refused after an equal one
+    was taken, and a tensor's value counts at the time of the call."""
+    import torch
+    assert D.dbl_workspace_bytes(D.DBL_OP_HEAD, 2, 1, 1, 8, 8) == 256
+    with pytest.raises(TypeError):
+        D.dbl_workspace_bytes(D.DBL_OP_HEAD, 2.0, 1, 1, 8, 8)
+    B = torch.tensor(32)
+    assert D.dbl_workspace_bytes(D.DBL_OP_HEAD, B, 1, 1, 8, 8) == 256
+    B.fill_(64)
+    assert D.dbl_workspace_bytes(D.DBL_OP_HEAD, B, 1, 1, 8, 8) == 512
+
+
 def _fake(n=1):
     # Non-null dummy addresses. Every call made with them below is invalid in some other
     # argument and must be rejected by host validation before anything is launched.
