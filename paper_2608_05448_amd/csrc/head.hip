@@ -1611,12 +1611,13 @@ __global__ __launch_bounds__(256) void lse_finalize_kernel(const float* __restri
 using HeadFew64 = FewCfg<256, 64, 2, 2, 1, 3>;
 using HeadFew128 = FewCfg<256, 128, 2, 4, 1, 3>;
 
+// Needs d % (64 C::KB) == 0: whole stages (both dispatchers see to it).
 template <class C, int EPI>
 hipError_t launch_few(const __bf16* h, const __bf16* w, const EpiArgs& ea, int64_t M, int64_t V,
                       int d, hipStream_t stream) {
   const int64_t dm = (M + C::BM - 1) / C::BM;
   const int64_t nwg = ((V + C::BV - 1) / C::BV) * dm;
-  if (nwg > 0x7fffffff || d % (64 * C::KB) != 0) return hipErrorInvalidConfiguration;
+  if (nwg > 0x7fffffff) return hipErrorInvalidConfiguration;
   hipLaunchKernelGGL((head_bf16_few_kernel<C, EPI>), dim3(static_cast<unsigned>(nwg)),
                      dim3(C::kThreads), 0, stream, h, w, ea, M, V, d, static_cast<int>(dm));
   return hipGetLastError();

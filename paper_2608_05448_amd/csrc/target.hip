@@ -334,15 +334,14 @@ __device__ void front_small(uint64_t* cand, int n, uint32_t tk) {
 // lower bound of the row's k-th largest s - in visiting order (s descending, id ascending),
 // applies both cuts and writes the kept tokens' log-probabilities; the rest of the output row
 // already holds -inf. Needs n >= k and n <= kCandCap; all kFT threads call it.
-// `least`: a key that at least k entries of the list reach (0 if none is known).
 __device__ void finish_candidates(const FilterArgs& a, float* out, uint64_t* cand, int n,
-                                  uint64_t* red, double* redd, uint32_t least) {
+                                  uint64_t* red, double* redd) {
   const int tid = threadIdx.x;
   const int k = static_cast<int>(a.top_k);
   // Wavefront 0: the k-th largest key of the list (bisection with ballots over the list) and
   // how many entries are at or above it.
   if (tid < 64) {
-    uint64_t lo = least, hi = 0xFFFFFFFFu;
+    uint64_t lo = 0, hi = 0xFFFFFFFFu;
     int c = 0;
     if (n <= 8 * 64) {  // up to 8 keys per lane, in registers; counts by ballot
       uint32_t kk[8];
@@ -544,7 +543,7 @@ __device__ bool filter_fast(const FilterArgs& a, const float* in, float* out, bo
   const int n = *sh_n;
   __syncthreads();
   if (n > kCandCap) return false;
-  finish_candidates(a, out, cand, n, red, redd, 0);
+  finish_candidates(a, out, cand, n, red, redd);
   return true;
 }
 
