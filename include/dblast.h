@@ -134,7 +134,9 @@ const char* dbl_last_error(void);
  *
  *   logit[m, v] = sum_j h[m*d + j] * w[v*d + j],   m < M = B*K*R, v < V
  *
- * in fp32 accumulation, written in the two-level form above; logits are never stored.
+ * in fp32 accumulation, written in the two-level form above; logits are never stored. A row's
+ * outputs do not depend on the other rows of the call or on its place among them (the order of
+ * the sum is a function of d and v alone), so a batch may be split in any way.
  *   dt     DBL_BF16 (bf16 h and w, MFMA path) or DBL_F32 (fp32 h and w)
  *   h      [B, K, R, d] row-major, element type dt: branch hidden states h_{k,z}
  *   w      [V, d] row-major (the lm_head.weight layout; the math weight is w^T), type dt
@@ -367,8 +369,9 @@ dbl_status dbl_prior_head(dbl_shape shape, const void* h_anchor, const void* U, 
  *   temperature  finite, >= 0;  top_k  >= 0 (0: off);  top_p  in (0, 1] (1: off)
  *   ws, ws_bytes optional workspace: NULL and 0, or dbl_workspace_bytes(DBL_OP_TARGET, shape)
  *                bytes (256-byte aligned) with shape.B * shape.K = N, shape.V = V. With it, rows
- *                with 0 < top_k <= 256 and V >= 16384 are split over several workgroups
- *                (faster when N is near or below the number of CUs); the output is the same.
+ *                of V >= 16384 under the temperature alone or 0 < top_k <= 256, and of V >= 32768
+ *                under top-p alone, are split over several workgroups (faster for every N, most
+ *                below the number of CUs); the output is the same.
  * Errors: DBL_EINVAL for null pointers, overlapping logits and logp, or parameters out of range;
  * DBL_ESHAPE; DBL_EWORKSPACE for a workspace that is too small or misaligned.
  */

@@ -79,6 +79,7 @@ CASES = [
     ("nucleus-top-k-ge-V", 2, 3000, 1.0, 5000, 0.8, False),
     ("nucleus-ragged-vocab", 3, 50001, 0.7, 0, 0.8, False),
     ("flat-row-nucleus", 2, 151936, 1.0, 0, 0.95, "flat"),
+    ("flat-row-nucleus-t07", 2, 40000, 0.7, 0, 0.95, "flat"),
     ("nucleus-cut-in-the-tail", 2, 151936, 1.0, 0, 0.9999999, "tail"),
 ]
 
@@ -147,8 +148,7 @@ def test_early_determinism_parity():
 
 # Rows split over workgroups, at the edges of their parts: two segments of 8192 ids exactly, one id
 # and one group of four more, a third segment of one id, one and two mass parts of 32,768, the share
-# counts' step at k = 128, a quarter of the vocabulary masked (whole shares without a bound), and
-# fewer ids allowed than k.
+# counts' step at k = 128, and a quarter of the vocabulary masked (whole shares without a bound).
 SPLIT_EDGES = [(f"{m}-{V}{'-' + t if t else ''}", 3, V, T, k, p, t)
                for V, t in ((16384, False), (16385, False), (16388, False), (24577, False),
                             (32768, False), (32771, False), (40000, "masked"))
@@ -185,6 +185,52 @@ FALLING = [(f"{t}-{V}-k{k}", 3, V, T, k, p, t)
            for V, T, k, p in ((151936, 0.7, 5, 0.95), (151936, 1.0, 100, 1.0), (151936, 0.7, 128, 0.95),
                               (151935, 1.3, 256, 1.0), (40001, 0.7, 128, 0.9), (16384, 1.0, 128, 1.0),
                               (16387, 1.0, 256, 0.95))]
+
+# Few allowed ids: fewer than k of them (the k-th largest is -inf and nothing is cut), just k and a few
+# more, scattered and in one share alone; shares without a bound, with and without enough threads that
+# hold an allowed id, and rows in which no share has one.
+ALLOWED = [(f"{n}-allowed-{'one-share' if lo else 'scattered'}-k{k}-p{p}", n, lo, k, p)
+           for n, lo in ((10, False), (10, True), (200, False), (200, True), (2500, True))
+           for k, p in ((20, 1.0), (20, 0.9), (200, 0.95), (256, 1.0))]
+
+
+@pytest.mark.parametrize("case", ALLOWED, ids=[c[0] for c in ALLOWED])
+def test_target_few_allowed_ids(case):
+    from paper_2608_05448_amd import dblast as D
+    name, n, one_share, k, p = case
+    N, V, T = 3, 40001, 0.7
+    rng = np.random.default_rng(len(name) + n)
+    lg = np.full((N, V), -np.inf, np.float32)
+    for r in range(N):
+        ids = 2600 + np.arange(n) if one_share else rng.permutation(V)[:n]
+        lg[r, ids] = 3.0 * rng.standard_normal(n)
+    lgd = torch.from_numpy(lg).cuda()
+    got = D.dbl_target_logprobs(lgd, T, k, p)
+    assert torch.equal(got, D.dbl_target_logprobs(lgd, T, k, p, split=False))
+    got, want = got.cpu().numpy(), TG.filter_logprobs(lg, T, k, p)
+    fin = np.isfinite(want)
+    assert np.array_equal(np.isfinite(got), fin)
+    assert np.max(np.abs(got[fin] - want[fin])) < 2e-6
+
+
+# The rows' and temperatures' ranges in which the transform divides in full: T beyond 2^-20 and 2^20 (the
+# logits scaled along, so that the distribution is the usual one), and a largest logit of 0.
+@pytest.mark.parametrize("T", [2.0 ** -21, 2.0 ** 21, 0.7])
+@pytest.mark.parametrize("p", [1.0, 0.9])
+@pytest.mark.parametrize("top_zero", [False, True])
+def test_target_division_ranges(T, p, top_zero):
+    from paper_2608_05448_amd import dblast as D
+    s = _logits(3, 40001, 17).astype(np.float64)
+    if top_zero:
+        s -= s.max(-1, keepdims=True)
+    lg = (s * T).astype(np.float32)
+    lgd = torch.from_numpy(lg).cuda()
+    got = D.dbl_target_logprobs(lgd, T, 0, p)
+    assert torch.equal(got, D.dbl_target_logprobs(lgd, T, 0, p, split=False))
+    got, want = got.cpu().numpy(), TG.filter_logprobs(lg, T, 0, p)
+    fin = np.isfinite(want)
+    assert np.array_equal(np.isfinite(got), fin)
+    assert np.max(np.abs(got[fin] - want[fin])) < 2e-6
 
 
 @pytest.mark.parametrize("case", FALLING, ids=[c[0] for c in FALLING])
