@@ -1281,7 +1281,7 @@ __global__ __launch_bounds__(kTopThreads) void filter_topk_share_kernel(FilterAr
   __syncthreads();
   // The share's largest key, by which the merge tells whether it needs a list that overflowed.
   uint32_t most = 0;
-  if (sh_n > cap) {  // workgroup-uniform
+  if (__builtin_expect(sh_n > cap, 0)) {  // workgroup-uniform
     most = top;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) most = max(most, static_cast<uint32_t>(__shfl_xor(most, o)));
@@ -1290,10 +1290,11 @@ __global__ __launch_bounds__(kTopThreads) void filter_topk_share_kernel(FilterAr
 #pragma unroll
     for (int w = 0; w < kTopThreads / 64; ++w)
       most = max(most, static_cast<uint32_t>(s_wave[0][w]));
+    most = order_key(__fdiv_rn(key_value(most), T));
   }
   if (tid == 0) {
     list[0] = (static_cast<uint64_t>(s_low) << 32) | static_cast<uint32_t>(sh_n);
-    list[1] = (static_cast<uint64_t>(order_key(__fdiv_rn(key_value(most), T))) << 32) |
+    list[1] = (static_cast<uint64_t>(most) << 32) |
               (jth > kKeyNegInf ? order_key(__fdiv_rn(key_value(jth), T)) : 0);
   }
 }
@@ -1322,59 +1323,65 @@ __global__ __launch_bounds__(kFT, 8) void filter_topk_merge_kernel(FilterArgs a,
   for (int i = 0; i < kTopEntries / kFT; ++i) e[i] = lists[tid + i * kFT];
   const uint64_t head = lists[(lane_id() % shares) * per];
   const uint64_t ends = lists[(lane_id() % shares) * per + 1];
-  uint32_t kth = static_cast<uint32_t>(head >> 32);
-  uint32_t jth = static_cast<uint32_t>(ends);
+  uint32_t kth = 0, jth = 0xFFFFFFFFu;  // over the 16 lanes that hold every share's heads, by scalar reads
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    kth = max(kth, static_cast<uint32_t>(__shfl_xor(kth, o)));
-    jth = min(jth, static_cast<uint32_t>(__shfl_xor(jth, o)));
+  for (int l = 0; l < 16; ++l) {
+    kth = max(kth, static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(head >> 32), l)));
+    jth = min(jth, static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(ends), l)));
   }
   const uint32_t least = max(kth, jth);
   // Shares whose list overflowed (logits that fall with the id, or coarse ones) and that hold a token
-  // that counts: their ids are read again, against the row's bound.
+  // that counts: their ids are read again, against the row's bound. The usual path, without any, comes
+  // first and shares no address with this one (its spills cost 0.5 us there).
   const uint64_t over = __ballot(lane_id() < shares &&
                                  static_cast<int>(static_cast<uint32_t>(head)) > per - 2 &&
                                  static_cast<uint32_t>(ends >> 32) >= least);
   if (tid == 0) sh_n = 0;
   __syncthreads();
-  auto keep = [&](uint64_t c) {
-    const int slot = atomicAdd(&sh_n, 1);
-    if (slot < kCandCap) cand[slot] = c;
-  };
+  if (__builtin_expect(over == 0, 1)) {
 #pragma unroll
-  for (int i = 0; i < kTopEntries / kFT; ++i) {
-    const int at = tid + i * kFT, share = at / per, slot = at % per;
-    const int cnt = static_cast<int>(static_cast<uint32_t>(__shfl(head, share)));
-    if (slot > 1 && slot < 2 + cnt && !(over >> share & 1) &&
-        static_cast<uint32_t>(e[i] >> 32) >= least)
-      keep(e[i]);
-  }
-  if (over && least) {
+    for (int i = 0; i < kTopEntries / kFT; ++i) {
+      const int at = tid + i * kFT, share = at / per, slot = at % per;
+      const int cnt = static_cast<int>(static_cast<uint32_t>(__shfl(head, share)));
+      if (slot > 1 && slot < 2 + cnt && static_cast<uint32_t>(e[i] >> 32) >= least)
+        cand[atomicAdd(&sh_n, 1)] = e[i];
+    }
+  } else if (least) {
     const float T = a.temperature;
     const uint32_t x_low =
         least_key([&](uint32_t q) { return order_key(__fdiv_rn(key_value(q), T)) >= least; });
+    auto keep = [&](uint64_t c) {
+      const int slot = atomicAdd(&sh_n, 1);
+      if (slot < kCandCap) cand[slot] = c;
+    };
     auto take = [&](int64_t v, float x) {
       if (order_key(x) >= x_low) keep(visit_key(order_key(__fdiv_rn(x, T)), v));
     };
-    for (uint64_t left = over; left; left &= left - 1) {
-      const auto [g0, g1, gfull] =
-          share_groups(V, shares, __ffsll(static_cast<unsigned long long>(left)) - 1);
-      int64_t i = g0 + tid;
+    for (int share = 0; share < shares; ++share) {
+      if (over >> share & 1) {
+        const auto [g0, g1, gfull] = share_groups(V, shares, share);
+        int64_t i = g0 + tid;
 #pragma unroll 4
-      for (; i < gfull; i += kFT) {
-        const f32x4u x = *reinterpret_cast<const f32x4u*>(in + 4 * i);
+        for (; i < gfull; i += kFT) {
+          const f32x4u x = *reinterpret_cast<const f32x4u*>(in + 4 * i);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) take(4 * i + q, x[q]);
+          for (int q = 0; q < 4; ++q) take(4 * i + q, x[q]);
+        }
+        if (i < g1)
+          for (int64_t v = 4 * i; v < V; ++v) take(v, in[v]);
+      } else {
+        const uint64_t* list = lists + share * per;
+        const int cnt = min(static_cast<int>(static_cast<uint32_t>(list[0])), per - 2);
+        for (int i = tid; i < cnt; i += kFT)
+          if (static_cast<uint32_t>(list[2 + i] >> 32) >= least) keep(list[2 + i]);
       }
-      if (i < g1)
-        for (int64_t v = 4 * i; v < V; ++v) take(v, in[v]);
     }
   }
   __syncthreads();
   const int n = sh_n;
   // Without a bound (too few threads of every share hold a logit above -inf) the lists hold all of
   // those logits, if none overflowed.
-  if (n > kCandCap || n < a.top_k || (over && !least)) {
+  if (__builtin_expect(n > kCandCap || n < a.top_k || (over && !least), 0)) {
     const bool vec = (V & 3) == 0 && (reinterpret_cast<uintptr_t>(in) & 15) == 0 &&
                      (reinterpret_cast<uintptr_t>(out) & 15) == 0;
     filter_general(a, in, out, vec, hist, red, redd, &sh_digit, &sh_above);
