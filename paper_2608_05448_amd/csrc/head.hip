@@ -1606,9 +1606,12 @@ __global__ __launch_bounds__(256) void lse_finalize_kernel(const float* __restri
 }
 
 // The head's tiles: one workgroup per CU over 256 weight rows, of four waves for up to 64 branch rows
-// (60 rows at d = 2560 149 us, where two workgroups of two waves over 128 weight rows took 160) and of
-// eight above.
+// (64 rows at d = 2560 148 us, where two workgroups of two waves over 128 weight rows took 164) and of
+// eight above. With fewer than kFewTiles tiles of 256 weight rows, tiles of 128 (64 rows at d = 4096:
+// 32,000 ids, 125 tiles, 59 -> 47 us, 1,000 ids 50 -> 44; at 50,257 ids, 197 tiles, 67 and 77).
+constexpr int64_t kFewTiles = 160;
 using HeadFew64 = FewCfg<256, 64, 2, 2, 1, 3>;
+using HeadFew64Short = FewCfg<128, 64, 1, 2, 1, 3>;
 using HeadFew128 = FewCfg<256, 128, 2, 4, 1, 3>;
 
 // Needs d % (64 C::KB) == 0: whole stages (both dispatchers see to it).
@@ -1654,12 +1657,15 @@ hipError_t launch_head(const HeadArgs& a, hipStream_t stream) {
       ea.lmass = a.lmass;
       ea.amax = amax;
       ea.nT = nT;
-      const hipError_t e =
-          a.M <= HeadFew64::BM
-              ? (amax ? launch_few<HeadFew64, kEpiLogSoftmaxArgmax>(h, w, ea, a.M, a.V, a.d, stream)
-                      : launch_few<HeadFew64, kEpiLogSoftmax>(h, w, ea, a.M, a.V, a.d, stream))
-              : (amax ? launch_few<HeadFew128, kEpiLogSoftmaxArgmax>(h, w, ea, a.M, a.V, a.d, stream)
-                      : launch_few<HeadFew128, kEpiLogSoftmax>(h, w, ea, a.M, a.V, a.d, stream));
+      auto few = [&](auto cfg) {
+        using C = decltype(cfg);
+        return amax ? launch_few<C, kEpiLogSoftmaxArgmax>(h, w, ea, a.M, a.V, a.d, stream)
+                    : launch_few<C, kEpiLogSoftmax>(h, w, ea, a.M, a.V, a.d, stream);
+      };
+      const hipError_t e = a.M > HeadFew64::BM ? few(HeadFew128{})
+                           : (a.V + HeadFew64::BV - 1) / HeadFew64::BV >= kFewTiles
+                               ? few(HeadFew64{})
+                               : few(HeadFew64Short{});
       if (e != hipSuccess) return e;
     } else if (a.d % PpCfg::BK == 0) {
       const int dm = static_cast<int>((a.M + PpCfg::BM - 1) / PpCfg::BM);

@@ -141,11 +141,11 @@ def test_head_random_shapes():
 # Few branch rows (up to 64 and up to 128 per launch, then the 256-row tiles): row counts at the edges
 # of the 32-row blocks and of both tiles, 1 to 5 and 64 stages of 64 hidden units (fewer than the ring
 # holds, and its wrap-around), vocabularies of one id, around one and two tiles and with every
-# remainder mod 4 (unaligned rows of the output).
+# remainder mod 4 (unaligned rows of the output), on both sides of 160 tiles of 256 ids.
 @pytest.mark.parametrize("M,d,V", [
     (1, 64, 1), (2, 64, 127), (31, 128, 129), (32, 192, 1001), (33, 256, 255), (63, 320, 1002),
     (64, 4096, 257), (65, 64, 1003), (95, 192, 259), (97, 128, 5000), (127, 320, 130),
-    (128, 4096, 513), (129, 64, 1001),
+    (128, 4096, 513), (129, 64, 1001), (33, 128, 40704), (64, 192, 40705), (5, 64, 41003),
 ])
 def test_head_few_rows(M, d, V):
     from paper_2608_05448_amd import dblast as D
@@ -185,11 +185,11 @@ def test_head_fp32_edges(M, d, V):
 # A row's log-probabilities depend neither on the other rows of the call nor on its place among them:
 # sharding a batch, or drafting one sequence of it alone, draws the same tokens. Row counts on both sides
 # of every change of kernel and tile, hidden sizes whose sum starts at 0 and, in the second group of 4096
-# ids, further on.
-@pytest.mark.parametrize("d", [64, 320, 2048, 4096])
-def test_head_rows_do_not_depend_on_the_batch(d):
+# ids, further on, vocabularies of fewer and of more than 160 tiles of 256 ids.
+@pytest.mark.parametrize("d,V", [(64, 5003), (320, 5003), (2048, 5003), (4096, 5003), (2048, 41003)])
+def test_head_rows_do_not_depend_on_the_batch(d, V):
     from paper_2608_05448_amd import dblast as D
-    M, V = 2100, 5003
+    M = 2100
     h = synth.make_uniform_logits((M, 1, 1, d), 71).to(torch.bfloat16)
     h[1500] = h[3]
     w = (synth.make_uniform_logits((V, d), 72) * (2.0 / math.sqrt(d))).to(torch.bfloat16)
