@@ -1270,7 +1270,7 @@ __global__ __launch_bounds__(512, 1) void head_bf16_pp_kernel(
 
   // The accumulators stay in the registers they were formed in: at two waves per SIMD all 256 are
   // addressable, and pinning them to the accumulation file, as before, cost the epilogue 670 moves per
-  // wave (a 512-row head at d = 1024 718 -> 710 us).
+  // wave (2048 rows at d = 1024 718 -> 710 us).
   // No memory half reads the slots any more (group 0 passed the barrier closing the last one;
   // group 1 reads none in its last compute half) and every copy has landed, so each wave stages
   // its stores in its own 16 KB of them.
@@ -1844,12 +1844,12 @@ hipError_t launch_expand(const ExpandArgs& a, hipStream_t stream) {
   // The largest tile that still gives kFill workgroups (larger tiles read less through the L2 per
   // weight row, smaller ones keep more CUs streaming), among those that are not mostly padding.
   // Measured, us by tile (rows x N x d: 128 x 256, 128 x 128, 128 x 64, 64 x 64, 64 x 32):
-  //   256 x 32768 x 4096: 80, 98, 123, 156, -     256 x 16384 x 4096: 62, 49, 61, 78, -
-  //   128 x 32768 x 4096: 77, 55, 69, 89, -       128 x 16384 x 4096: 56, 45, 37, 44, -
-  //    60 x 32768 x 4096: 69, 50, 43, 51, 72      256 x 10240 x 2560: 50, 34, 46, 44, -
-  //    15 x 32768 x 4096: 64, 49, 42, 46, 46      128 x 10240 x 2560: 47, 36, 27, 32, 38
-  //   256 x  4096 x 2048: 38, 25, 20, 15, 22       60 x 10240 x 2560: 42, 30, 28, 19, 27
-  //    60 x  4096 x 2048: 33, 22, 20, 15, 12       15 x 10240 x 2560: 35, 27, 24, 17, 15
+  //   256 x 32768 x 4096: 80, 100, 121, 153, 280    256 x 16384 x 4096: 63, 49, 61, 77, 142
+  //   128 x 32768 x 4096: 72, 55, 68, 87, 139       128 x 16384 x 4096: 55, 45, 37, 42, 70
+  //    60 x 32768 x 4096: 66, 49, 42, 47, 72        256 x 10240 x 2560: 48, 33, 45, 42, 65
+  //    15 x 32768 x 4096: 62, 48, 40, 40, 42        128 x 10240 x 2560: 45, 34, 26, 31, 37
+  //   256 x  4096 x 2048: 34, 23, 18, 14, 21         60 x 10240 x 2560: 41, 29, 26, 18, 26
+  //    60 x  4096 x 2048: 32, 22, 18, 14, 11         15 x 10240 x 2560: 34, 26, 23, 16, 14
   constexpr int64_t kFill = 160;
   if (a.M > 128 && tiles(128, 256) >= kFill) return launch_expand_rs<RsNarrow>(a, N, stream);
   if (a.M > 64 && tiles(128, 128) >= kFill) return launch_expand_few<Few128x128>(a, N, stream);
