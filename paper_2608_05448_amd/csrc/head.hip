@@ -503,18 +503,17 @@ __global__ __launch_bounds__(C::kThreads, 1) void head_bf16_kernel(
 // time, so that a row's result depends neither on the other rows of the call nor on its place among
 // them. The sum starts at unit walk_start, runs to d and wraps around. It starts at 0 unless the operand
 // rows are a multiple of 4 KB apart: workgroups that walk such rows from the same unit all load from the
-// same few memory channels, so each group of weight rows starts 640 units after the one before it. The
-// expander takes groups of 1024 rows (15 trunk rows against 32768 x 4096 56 -> 40 us, 128 rows 61 -> 56;
-// with 4096 41). The head takes 4096: 8, 60 and 120 rows against 151936 x 4096 229, 238 and 258 ->
-// 213, 218 and 242 us, while the 256-row kernel, whose tiles share operand slabs in the L2 only as long as
-// they walk together, is 0.5% slower than from 0 (1.3% with 2048, 2% with 1024). A start is a multiple
-// of 128 units, the deepest stage of any kernel.
-constexpr int kWalkExpand = 1024;
-constexpr int kWalkHead = 4096;
+// same few memory channels, so each group of weight rows starts some units after the one before it. The
+// expander takes groups of 1024 rows and 640 units (15 trunk rows against 32768 x 4096 56 -> 40 us, 128
+// rows 61 -> 56; with groups of 4096 41). The head takes 4096 rows and 1024 units: 8, 60 and 120 rows
+// against 151936 x 4096 229, 236 and 243 -> 210, 215 and 238 us; the 256-row kernel, whose tiles share
+// operand slabs in the L2 only as long as they walk together, loses 0.1 to 0.4% of 2011 us at 2048 rows (1%
+// with groups of 2048, 2% with 1024; a start per XCD gained it 1.7%, but made a row's result depend on its
+// place in the batch). A start is a multiple of 128 units, the deepest stage of any kernel.
 template <bool EXPAND>
 __device__ __forceinline__ int walk_start(int64_t v0, int d) {
-  return d % 2048 == 0 ? 128 * (5 * static_cast<int>(v0 / (EXPAND ? kWalkExpand : kWalkHead)) % (d / 128))
-                       : 0;
+  constexpr int kRows = EXPAND ? 1024 : 4096, kUnits = EXPAND ? 640 : 1024;
+  return d % 2048 == 0 ? static_cast<int>(v0) / kRows * kUnits % d : 0;
 }
 
 // ---------------------------------------------------------------------------------------
