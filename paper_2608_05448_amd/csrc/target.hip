@@ -1137,8 +1137,8 @@ __device__ __forceinline__ uint32_t least_key(F ok) {
 // j = ceil(k / shares). A merge workgroup per row keeps the tokens that reach the largest of the
 // shares' bounds and the least of their j-th largest (j tokens of every share reach that one, so
 // the row's k-th largest does): two or three times k of them, selects among them and finishes.
-// 16 rows of 151,936 at k = 50: 11.5 + 7.1 us, against 23 + 54 us with 4 shares per row, bounds per
-// wavefront and a merge that bisected 1,600 candidates; 272 rows at k = 20 84 us (112).
+// 16 rows of 151,936 at k = 50: 10.7 + 7.5 us, against 23 + 54 us with 4 shares per row, bounds per
+// wavefront and a merge that bisected 1,600 candidates; 272 rows at k = 20 82 us (112).
 // 16 shares per row up to k = 128, 8 above: k tokens per share and the overshoot stay within a
 // share's list, and the smallest row (kSplitMinV) still has more non-empty threads than k. Where the
 // logits fall with the id a thread holds several of the largest and its neighbours the next, so up to 4 k
