@@ -239,3 +239,18 @@ def test_head_fp32_tile_rule(M, d, V):
     h = synth.make_uniform_logits((M, 1, 1, d), 63).to(torch.float32)
     w = (synth.make_uniform_logits((V, d), 64) / math.sqrt(d)).to(torch.float32)
     _check(h, w, 2e-5, "fp32-tile-rule")
+
+
+# The same for hidden sizes that 64 does not divide, and for fp32 rows in tiles of four and of sixteen.
+@pytest.mark.parametrize("dt,d,V", [(torch.bfloat16, 96, 1003), (torch.bfloat16, 40, 1003),
+                                    (torch.float32, 512, 38400), (torch.float32, 320, 38401)])
+def test_other_head_rows_do_not_depend_on_the_batch(dt, d, V):
+    from paper_2608_05448_amd import dblast as D
+    M = 300
+    h = synth.make_uniform_logits((M, 1, 1, d), 73).to(dt).cuda()
+    w = (synth.make_uniform_logits((V, d), 74) * (2.0 / math.sqrt(d))).to(dt).cuda()
+    whole = D.dbl_head_logprobs(h, w, argmax=True)
+    for lo, n in ((4, 1), (0, 11), (20, 33), (40, 129)):
+        part = D.dbl_head_logprobs(h[lo:lo + n].contiguous(), w, argmax=True)
+        for a, b in zip(whole, part):
+            assert torch.equal(a[lo:lo + n], b), (dt, d, lo, n)
